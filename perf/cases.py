@@ -229,6 +229,90 @@ def run(state):
     return _RUN[state["case"]["kind"]](state, state["case"])
 
 
+def _factor(amax, case):
+    """(stored scale, multiplier) of groups with these maxima, in FP32 as the format fixes it; power-of-two scales are
+    rounded up."""
+    amax = amax.float()
+    if case["scales"] == "pow2":
+        m, e = torch.frexp(amax / 448.0)
+        s = torch.ldexp(torch.ones_like(amax), torch.where(m == 0.5, e - 1, e))
+        r = 1.0 / s
+    else:
+        s, r = amax / 448.0, torch.full_like(amax, 448.0) / amax
+    return torch.where(amax == 0, 1.0, s), torch.where(amax == 0, 0.0, r)
+
+
+def _rounded(x, case, rows, cols):
+    """`x` as its codes and scales hold it, in 64 bits: groups of rows x cols, E4M3 codes."""
+    m, k = x.shape
+    xp = torch.nn.functional.pad(x.float(), (0, -k % cols, 0, -m % rows))
+    g = xp.view(xp.shape[0] // rows, rows, xp.shape[1] // cols, cols)
+    s, r = _factor(g.abs().amax((1, 3), keepdim=True), case)
+    return ((g * r).to(torch.float8_e4m3fn).double() * s.double()).view(xp.shape)[:m, :k]
+
+
+def _decoded(q, s, rows):
+    """Codes and scales (groups of rows x 128) in 64 bits."""
+    q, s = q.contiguous().view(torch.float8_e4m3fn).double(), s.double()
+    return q * s.repeat_interleave(rows, 0).repeat_interleave(128, 1)[: q.shape[0], : q.shape[1]]
+
+
+def _silu_mul(h):
+    g, u = h.double().chunk(2, 1)
+    return (g * torch.sigmoid(g) * u).bfloat16()         # a BF16 tensor, whoever produces it
+
+
+def _exact_bwd(s, case):
+    dy = s["dy"]
+    dx = _rounded(dy, case, 1, 128) @ _decoded(s["wt"], s["swt"], 128).t()
+    if case["cache"] == "bf16":
+        x = s["x"]
+    elif case["cache"] == "fp8":
+        x = _decoded(*s["x"], 1).float()                 # the re-tiled values are FP32 products
+    else:
+        q, sc = s["x"]
+        b = q.int().view(q.shape[0], -1, 3)              # two 12-bit codes in three bytes: the upper bits of binary16
+        c = torch.stack((b[..., 0] | (b[..., 1] & 15) << 8, b[..., 1] >> 4 | b[..., 2] << 4), -1).view(q.shape[0], -1)
+        x = (c << 4).to(torch.int16).view(torch.float16).float() * sc.repeat_interleave(128, 1)[:, : c.shape[1]]
+    return dx, _rounded(dy, case, 128, 1).t() @ _rounded(x, case, 128, 1)
+
+
+def _exact_moe(s, case):
+    h, i, y = case["hidden"], case["inter"], []
+    off = s["off"].tolist()
+    for e in range(case["experts"]):
+        x = _rounded(s["x"][off[e] : off[e + 1]], case, 1, 128)
+        gu = (x @ _decoded(s["w13"][0][e], s["w13"][1][e], 128).t()).bfloat16()
+        gu = gu.view(-1, i // 128, 2, 128).transpose(1, 2).reshape(-1, 2 * i)
+        y.append(_rounded(_silu_mul(gu), case, 1, 128) @ _decoded(s["w2"][0][e], s["w2"][1][e], 128).t())
+    return torch.cat(y)
+
+
+def _exact_update(s, case):
+    w, g, m, v = (s[t].double() for t in ("w", "grad", "m", "v"))
+    t = s["step"] + 1
+    m, v = 0.9 * m + 0.1 * g, 0.95 * v + 0.05 * g * g
+    w = w - 2.2e-4 * (m / (1 - 0.9**t) / ((v / (1 - 0.95**t)).sqrt() + 1e-8) + 0.1 * w)
+    return w, m, v, w.view_as(s["w_bf16"]), None
+
+
+def exact(case, seed):
+    """What `run` returns, with the codes and scales as the formats fix them and every sum in 64 bits; no value for
+    codes, whose bits are compared as they are."""
+    s = prepare(case, seed)
+    if case["kind"] != "fwd":
+        return {"bwd": _exact_bwd, "moe": _exact_moe, "update": _exact_update}[case["kind"]](s, case)
+    x = s["x"]
+    if case["pre"] == "swiglu":
+        x = _silu_mul(x)
+    elif case["pre"] == "rmsnorm":
+        x = x.double()
+        x = (x * (x.square().mean(1, keepdim=True) + 1e-6).rsqrt() * s["gamma"].double()).bfloat16()
+    w = _rounded(s["w"], case, 128, 128) if case["weights"] == "fresh" else _decoded(*s["w"], 128)
+    y = _rounded(x, case, 1, 128) @ w.t()
+    return {"none": y, "fp8": (y, None, None), "e5m6": (y, None)}[case["cache"]]
+
+
 def _codes(rows, cols):
     """Bytes of 1x128-quantized codes and their scales."""
     return rows * cols + rows * ((cols + 127) // 128) * 4
