@@ -140,7 +140,8 @@ ds3_status ds3_quant_w_128x128(const void* w, ds3_dtype wt, int64_t n, int64_t k
  * in K order by whichever workgroup completes a tile (Section 3.3.2 leaves the
  * order of the FP32 additions open).  Pass ds3_gemm_workspace_bytes() bytes to
  * allow it, or NULL (with any size) to forbid it; a non-NULL workspace that is
- * too small is DS3_ERR_WORKSPACE.  Results are deterministic for a given shape
+ * too small is DS3_ERR_WORKSPACE.  (Calls of few rows or few tiles divide K inside
+ * a workgroup instead and leave the workspace alone.)  Results are deterministic for a given shape
  * and workspace choice, but not bit-comparable across shapes or between a
  * call with and a call without workspace.
  */

@@ -118,4 +118,14 @@ __device__ __forceinline__ unsigned int cvt4_e4m3(float a, float b, float c, flo
     return (unsigned int)w;
 }
 
+// ---- shared by the GEMM kernels -----------------------------------------------------
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// XOR key of a tile row: depends on the row's position inside its 16-row fragment only.
+__device__ __forceinline__ int swz_key(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
+// Offset that is out of range for every descriptor the GEMM kernels build (their
+// sizes are below 2^31): a load with it moves no data.
+constexpr unsigned kOobOffset = 0x80000000u;
+
 }  // namespace ds3

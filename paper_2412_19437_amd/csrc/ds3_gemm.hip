@@ -34,8 +34,6 @@
 
 namespace ds3 {
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
 constexpr int kMaxGroups = 1023;                       // experts per grouped call (prefix table in LDS)
 constexpr int kShareSkew = 6;                          // K-steps by which the two pieces of a halved tile differ, each way
 constexpr int kAuxDevice = 16;                         // cache policy of a buffer access: sc1, coherent across the device
@@ -81,13 +79,6 @@ __host__ __device__ inline bool tail_worth_sharing(int rounds, int tail, int nsl
     if (tail <= 0) return false;
     return rounds == 0 ? 5 * tail <= 3 * nslots : 3 * tail <= nslots;
 }
-
-// XOR key of a tile row: depends on the row's position inside its 16-row fragment only.
-__device__ __forceinline__ int swz_key(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-// Offset that is out of range for every descriptor this kernel builds (their
-// sizes are below 2^31): a load with it moves no data.
-constexpr unsigned kOobOffset = 0x80000000u;
 
 // What a workgroup needs to know about one output tile (all wave-uniform
 // except the two per-thread scale pointers).
@@ -1019,7 +1010,19 @@ static int default_variant(const GemmParams& p, ds3_bscale mode) {
 
 ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, void* ws, size_t ws_bytes,
                        hipStream_t st) {
-    if (variant < 0) variant = default_variant(p, mode);
+    if (variant < 0) {
+        variant = default_variant(p, mode);
+        if (p.G == 0 && gemm_skinny_preferred(p, num_cus_x8())) {
+            // (this kernel needs no workspace; one that is too small for the shape's tile walk is an error all the same)
+            if (ws != nullptr) {
+                size_t need = 0;
+                const ds3_status rc = launch_variant<false>(p, ct, mode, variant, nullptr, 0, &need, st);
+                if (rc != DS3_OK) return rc;
+                if (ws_bytes < need) return DS3_ERR_WORKSPACE;
+            }
+            return launch_gemm_skinny(p, ct, mode, pow2, num_cus_x8(), st);
+        }
+    }
     return pow2 ? launch_variant<true>(p, ct, mode, variant, ws, ws_bytes, nullptr, st)
                 : launch_variant<false>(p, ct, mode, variant, ws, ws_bytes, nullptr, st);
 }

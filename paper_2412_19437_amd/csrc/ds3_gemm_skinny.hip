@@ -1,0 +1,301 @@
+// Block-scaled FP8 GEMM for few activation rows or few output tiles (decode
+// batches, small layers, the weight gradient of a narrow layer): the product of
+// ds3_gemm.hip, split for a different bound.
+//
+// Such a call is not bound by the matrix pipe but by how many bytes are in flight
+// and by how long one workgroup's K-loop is.  The main kernel's 128x128 tiles
+// leave most compute units without work, keep LDS for activation rows that do
+// not exist, and walk all of K one step after another.  Here a workgroup takes
+// BN weight rows by BM activation rows with NS stages in LDS, NS-1 of them in
+// flight, and WK groups of waves take every WK-th K-step each; their partial
+// sums meet in LDS in fixed order (no workspace, no second kernel, the result
+// does not depend on timing).
+//
+// Measured against the main kernel on MI355X, weights from HBM (us, before -> now;
+// M x N x K): 32x18432x7168 52 -> 31 (2.8 -> 4.3 TB/s of weights), 32x4096x7168
+// 33 -> 12, 256x512x1024 9.4 -> 3.4, 512x2048x2048 12.9 -> 8.0, 1024x1024x4096
+// 19.6 -> 11.6; per-row scales, FP32 output: 512x1024x4096 19.9 -> 9.0.
+// What is left at 32 rows is the ramp and the drain of one round of tiles; the
+// smallest calls are a launch and one latency per stage.
+#include "ds3_dev.h"
+#include "ds3_internal.h"
+
+namespace ds3 {
+
+template <int FN_, int FM_, int WN_, int WK_, int NS_>
+struct SkinnyCfg {
+    static constexpr int FN = FN_, FM = FM_, WN = WN_, WK = WK_, NS = NS_;
+    static constexpr int NT = 64 * WN * WK;
+    static constexpr int BN = WN * FN * 16, BM = FM * 16;
+    static constexpr int ROWS = BN + BM;               // rows of one K-step's codes
+    static constexpr int GROUP = ROWS * 128;           // bytes of codes per K-step
+    static constexpr int NSA = (BM + 63) / 64;         // activation-scale loads per wave and stage (one row a lane)
+    static constexpr int SCALES = (NSA + 1) * 256;     // per wave and stage: the activation scales, then the weight block's
+    static constexpr int STAGE = WK * GROUP + WN * WK * SCALES;
+    static constexpr int NB = 2 * FN, NA = BM / (8 * WN);      // code loads per thread and stage: weights, activations
+    static constexpr int LOADS = NB + NA + NSA + 1;         // vector-memory operations per wave and stage
+    static constexpr int RLD = BN + 4;                 // floats per row of the reduction buffer
+    static constexpr int RED = WK * BM * RLD * 4;
+    static constexpr int LDS_BYTES = (NS * STAGE > RED ? NS * STAGE : RED);
+    static_assert(BM % (8 * WN) == 0, "load mapping");
+    static_assert(FN * 16 <= 64, "one weight-scale block per wave, one weight row a lane");
+    static_assert(NS >= 2 && (NS - 2) * LOADS < 64, "vmcnt immediate");
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+template <class C, bool ROWSB, bool OUT_BF16, bool POW2>
+__global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) {
+    constexpr int FN = C::FN, FM = C::FM, WN = C::WN, WK = C::WK, NS = C::NS, BN = C::BN, BM = C::BM;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[C::LDS_BYTES];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, wk = wave / WN;
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const int KB = p.K >> 7;
+
+    // ---- which tile: the tile list is cut into one contiguous chunk per XCD (workgroups are dealt
+    // round robin to them), row tiles innermost, so that those which share weights share an L2
+    const int ntiles = p.tiles_m * p.tiles_n, per_xcd = (ntiles + 7) >> 3;
+    const int local = (int)(blockIdx.x >> 3), t = (int)(blockIdx.x & 7) * per_xcd + local;
+    if (local >= per_xcd || t >= ntiles) return;
+    const int n0 = t / p.tiles_m * BN, m0 = t % p.tiles_m * BM;
+    const int m_rows = min(p.M - m0, BM);
+    const int n_rows = min(p.N - n0, BN);
+
+    // Descriptors over the tile's valid bytes: rows beyond them move no data.
+    const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.a + (int64_t)m0 * p.lda), 0, (int)((int64_t)(m_rows - 1) * p.lda + p.K), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.b + (int64_t)n0 * p.ldb), 0,
+        (int)((int64_t)(n_rows - 1) * p.ldb + p.K), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_sa = __builtin_amdgcn_make_buffer_rsrc((void*)p.sa, 0, 0x7ffffffc, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_sb = __builtin_amdgcn_make_buffer_rsrc((void*)p.sb, 0, 0x7ffffffc, 0x00020000);
+
+    // Each group of WN waves moves the rows of its own K-step, 8 * WN per load; 16-byte chunks are
+    // XOR-swizzled by row so that a fragment read spreads over the banks.
+    const int lrow = wn * 8 + (lane >> 3);
+    const int gchunk = (lane & 7) ^ swz_key(lrow);
+    const unsigned voff_b = (unsigned)(lrow * (int)p.ldb + gchunk * 16), voff_a = (unsigned)(lrow * (int)p.lda + gchunk * 16);
+    const unsigned step_b = (unsigned)(8 * WN * (int)p.ldb), step_a = (unsigned)(8 * WN * (int)p.lda);
+    // scales: each wave fetches for itself, an activation row's per lane, and its weight block's or (per-row
+    // mode) a weight row's per lane; what lies beyond the last row repeats it
+    unsigned soff_a[C::NSA];
+#pragma unroll
+    for (int h = 0; h < C::NSA; ++h) soff_a[h] = (unsigned)((m0 + min(h * 64 + lane, m_rows - 1)) * (int)p.sar) * 4u;
+    const int sb_row = ROWSB ? n0 + min(wn * FN * 16 + lane, n_rows - 1) : min((n0 + wn * FN * 16) >> 7, ((p.N + 127) >> 7) - 1);
+    unsigned soff_b = (unsigned)(sb_row * (int)p.sbr) * 4u;
+    unsigned sa_step = (unsigned)p.sak * 4u, sb_step = (unsigned)p.sbk * 4u;   // read once, not from the kernel arguments in the loop
+    asm volatile("" : "+v"(soff_b), "+s"(sa_step), "+s"(sb_step));
+
+    uint8_t* const codes = smem + wk * C::GROUP;                            // + stage * STAGE
+    uint8_t* const scales = smem + WK * C::GROUP + wave * C::SCALES;        // + stage * STAGE
+    auto issue = [&](int step, int stage) {
+        const int kb = step * WK + wk;
+        const unsigned koff = kb < KB ? (unsigned)kb << 7 : kOobOffset;
+        const int kc = min(kb, KB - 1);
+        uint8_t* dst = codes + stage * C::STAGE + wn * 1024;
+#pragma unroll
+        for (int i = 0; i < C::NB + C::NA; ++i) {
+            const bool is_b = i < C::NB;
+            const unsigned voff = is_b ? voff_b + (koff + (unsigned)i * step_b) : voff_a + (koff + (unsigned)(i - C::NB) * step_a);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(is_b ? rs_b : rs_a, (lds_ptr_t)(dst + i * (WN * 1024)), 16, (int)voff, 0, 0, 0);
+        }
+        uint8_t* sd = scales + stage * C::STAGE;
+#pragma unroll
+        for (int h = 0; h < C::NSA; ++h)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_sa, (lds_ptr_t)(sd + h * 256), 4, (int)(soff_a[h] + (unsigned)kc * sa_step), 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_sb, (lds_ptr_t)(sd + C::NSA * 256), 4, (int)(soff_b + (unsigned)kc * sb_step), 0, 0, 0);
+    };
+    const int key = swz_key(l16);
+    const int foff0 = l16 * 128 + (((2 * g4) ^ key) << 4), foff1 = l16 * 128 + (((2 * g4 + 1) ^ key) << 4);
+    auto load_frag = [&](const uint8_t* base) -> i32x8 {
+        const i32x4 lo = *reinterpret_cast<const i32x4*>(base + foff0);
+        const i32x4 hi = *reinterpret_cast<const i32x4*>(base + foff1);
+        return i32x8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    };
+
+    const int steps = (KB + WK - 1) / WK;
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) issue(s, s);
+    f32x4 acc[FN][FM];
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    int stage = 0;
+    for (int s = 0; s < steps; ++s) {
+        // This step's loads have landed (those of the NS-2 steps behind it stay in flight), in every
+        // wave once the barrier is passed; and every wave is done with the stage read before it.
+        asm volatile("" ::: "memory");
+        constexpr int keep = (NS - 2) * C::LOADS;
+        __builtin_amdgcn_s_waitcnt((keep & 15) | ((keep >> 4) << 14) | 0x70);      // vmcnt(keep) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const uint8_t* st = codes + stage * C::STAGE;
+        const float* sc = reinterpret_cast<const float*>(scales + stage * C::STAGE);
+        // (everything that is read from LDS in this step is read before the next loads are issued: the
+        // compiler makes an LDS read behind LDS-bound loads wait for them)
+        i32x8 w[FN], x[FM];
+        float sav[FM];
+        const float* sbs = sc + C::NSA * 64;
+        [[maybe_unused]] const float sbv = ROWSB ? 1.f : sbs[0];
+        [[maybe_unused]] f32x4 un[FN];                 // per-row mode: scales of the four weight rows a lane's sums belong to
+        [[maybe_unused]] float ur[FN];                 // ... and of the row whose codes it feeds (power-of-two scales)
+        if constexpr (ROWSB) {
+#pragma unroll
+            for (int i = 0; i < FN; ++i) {
+                un[i] = *reinterpret_cast<const f32x4*>(sbs + i * 16 + g4 * 4);
+                ur[i] = sbs[i * 16 + l16];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < FM; ++j) sav[j] = sc[j * 16 + l16];
+#pragma unroll
+        for (int i = 0; i < FN; ++i) w[i] = load_frag(st + (wn * FN + i) * 2048);
+#pragma unroll
+        for (int j = 0; j < FM; ++j) x[j] = load_frag(st + (BN + j * 16) * 128);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(s + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s * WK + wk < KB) {
+#pragma unroll
+            for (int j = 0; j < FM; ++j) {
+#pragma unroll
+                for (int i = 0; i < FN; ++i) {
+                    if constexpr (POW2) {
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                            w[i], x[j], acc[i][j], 0, 0, 0, (int)(as_u32(ROWSB ? ur[i] : sbv) >> 23), 0, (int)(as_u32(sav[j]) >> 23));
+                    } else {
+                        const f32x4 pr = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w[i], x[j], f32x4{0.f, 0.f, 0.f, 0.f},
+                                                                                         0, 0, 0, 0, 0, 0);
+                        f32x4 t;                       // (the rescale of ds3_gemm.hip)
+                        if constexpr (ROWSB) t = f32x4{sav[j] * un[i].x, sav[j] * un[i].y, sav[j] * un[i].z, sav[j] * un[i].w};
+                        else t.x = t.y = t.z = t.w = sav[j] * sbv;
+                        acc[i][j].x = __builtin_fmaf(pr.x, t.x, acc[i][j].x);
+                        acc[i][j].y = __builtin_fmaf(pr.y, t.y, acc[i][j].y);
+                        acc[i][j].z = __builtin_fmaf(pr.z, t.z, acc[i][j].z);
+                        acc[i][j].w = __builtin_fmaf(pr.w, t.w, acc[i][j].w);
+                    }
+                }
+            }
+        }
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+
+    // ---- the groups' sums meet in LDS: [wk][row][column] ----
+    __builtin_amdgcn_s_waitcnt(0x70);                  // no load is on its way into the stages any more
+    __syncthreads();
+    float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int j = 0; j < FM; ++j)
+#pragma unroll
+        for (int i = 0; i < FN; ++i)
+            *reinterpret_cast<f32x4*>(red + (wk * BM + j * 16 + l16) * C::RLD + (wn * FN + i) * 16 + g4 * 4) = acc[i][j];
+    __syncthreads();
+    auto sum4 = [&](int row, int col) -> f32x4 {
+        f32x4 v = *reinterpret_cast<const f32x4*>(red + row * C::RLD + col);
+#pragma unroll
+        for (int g = 1; g < WK; ++g) {
+            const f32x4 o = *reinterpret_cast<const f32x4*>(red + (g * BM + row) * C::RLD + col);
+            v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
+        return v;
+    };
+    for (int idx = tid; idx < m_rows * (BN / 4); idx += C::NT) {
+        const int row = idx / (BN / 4), col = idx % (BN / 4) * 4;
+        if (col >= n_rows) continue;
+        f32x4 v = sum4(row, col);
+        const int64_t at = (int64_t)(m0 + row) * p.ldc + n0 + col;
+        if constexpr (OUT_BF16) {
+            uint16_t* d = static_cast<uint16_t*>(p.c) + at;
+            const u32x2 o = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+            if (col + 4 <= n_rows) *reinterpret_cast<u32x2*>(d) = o;
+            else for (int q = 0; col + q < n_rows; ++q) d[q] = (uint16_t)((q & 2 ? o.y : o.x) >> (16 * (q & 1)));
+        } else {
+            float* d = static_cast<float*>(p.c) + at;
+            if (col + 4 <= n_rows) {
+                if (p.accumulate) {
+                    const f32x4 old = *reinterpret_cast<const f32x4*>(d);
+                    v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+                }
+                *reinterpret_cast<f32x4*>(d) = v;
+            } else {
+                const float o[4] = {v.x, v.y, v.z, v.w};
+                for (int q = 0; col + q < n_rows; ++q) d[q] = p.accumulate ? d[q] + o[q] : o[q];
+            }
+        }
+    }
+}
+
+// ---- host side -------------------------------------------------------------------
+template <class C, bool ROWSB, bool POW2>
+static ds3_status launch_one(GemmParams p, ds3_dtype ct, hipStream_t st) {
+    p.tiles_m = (p.M + C::BM - 1) / C::BM;
+    p.tiles_n = (p.N + C::BN - 1) / C::BN;
+    const dim3 grid((unsigned)(((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8));
+    (void)hipGetLastError();                            // a stale error of earlier, unrelated work is not this launch's
+    if (ct == DS3_BF16) gemm_skinny_kernel<C, ROWSB, true, POW2><<<grid, dim3(C::NT), 0, st>>>(p);
+    else gemm_skinny_kernel<C, ROWSB, false, POW2><<<grid, dim3(C::NT), 0, st>>>(p);
+    return hipGetLastError() == hipSuccess ? DS3_OK : DS3_ERR_LAUNCH;
+}
+
+template <class C>
+static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, bool row_scales, bool pow2, hipStream_t st) {
+    if (row_scales) return pow2 ? launch_one<C, true, true>(p, ct, st) : launch_one<C, true, false>(p, ct, st);
+    return pow2 ? launch_one<C, false, true>(p, ct, st) : launch_one<C, false, false>(p, ct, st);
+}
+
+// The configurations and what a call takes with each: `fixed` + one round of tiles after another, a
+// round being K-steps / WK stages of `full` us when every workgroup slot has a tile and `alone` us when
+// few have, plus the sums' way out.  The figures are fits to measured times of 72 shapes (M 1 .. 2048,
+// N 512 .. 24576, K 512 .. 7168, weights from HBM), within 9-14% of each configuration's own; the
+// configuration they pick is on average 4% slower than the best of ten that were tried, 22% at worst.
+struct SkinnyChoice { int bn, bm, wk, per_cu; float alone, full, out, fixed; };
+constexpr int kSkinnyCfgs = 5;
+constexpr SkinnyChoice kSkinny[kSkinnyCfgs] = {
+    {32, 32, 4, 1, 0.40f, 0.55f, 1.5f, 1.5f},
+    {32, 32, 2, 2, 0.25f, 0.50f, 1.0f, 1.5f},
+    {128, 32, 2, 1, 0.55f, 0.70f, 1.5f, 1.5f},
+    {64, 64, 2, 1, 0.50f, 0.65f, 1.5f, 1.5f},
+    {128, 64, 1, 2, 0.45f, 0.85f, 1.5f, 2.0f},
+};
+
+static int skinny_choice(int M, int N, int K, int cus) {
+    int best = 0;
+    float best_us = 0.f;
+    for (int i = 0; i < kSkinnyCfgs; ++i) {
+        const SkinnyChoice& c = kSkinny[i];
+        const int64_t tiles = (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn), slots = (int64_t)cus * c.per_cu;
+        const float steps = (float)((K / 128 + c.wk - 1) / c.wk);
+        const int64_t rest = tiles % slots;
+        float us = c.fixed + (float)(tiles / slots) * (steps * c.full + c.out);
+        if (rest) us += steps * (c.alone + (c.full - c.alone) * ((float)rest / (float)slots)) + c.out;
+        if (i == 0 || us < best_us) { best = i; best_us = us; }
+    }
+    return best;
+}
+
+// Few rows (nothing is gained from a second row tile: 64x32768x3072 33-38 -> 24 us), or fewer 128x128
+// tiles than compute units.  From there on the main kernel's larger tiles win (us, main / this one:
+// 226 tiles 305x14386x1664 22-29 / 24, 240 tiles 1877x1250x3072 21-23 / 20, 256 tiles 1024x4096x7168
+// 47 / 50, 270 tiles 1152x3712x1536 16 / 20, 384 tiles 2048x3000x1536 16 / 18).
+bool gemm_skinny_preferred(const GemmParams& p, int cus) {
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
+    if (p.M > 64 && tiles >= cus) return false;
+    // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel
+    return (int64_t)129 * p.ldb + p.K < (1ll << 31) && (int64_t)65 * p.lda + p.K < (1ll << 31) && p.N < (1 << 26);
+}
+
+ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st) {
+    const bool rows = mode == DS3_BSCALE_PER_ROW;
+    switch (skinny_choice(p.M, p.N, p.K, cus)) {
+        case 0: return launch_cfg<SkinnyCfg<1, 2, 2, 4, 4>>(p, ct, rows, pow2, st);
+        case 1: return launch_cfg<SkinnyCfg<1, 2, 2, 2, 4>>(p, ct, rows, pow2, st);
+        case 2: return launch_cfg<SkinnyCfg<2, 2, 4, 2, 3>>(p, ct, rows, pow2, st);
+        case 3: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
+        default: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
+    }
+}
+
+}  // namespace ds3

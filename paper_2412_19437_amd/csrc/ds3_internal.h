@@ -71,6 +71,10 @@ struct GemmParams {
 // ws / ws_bytes: device workspace for sharing tail tiles along K (nullptr: never share).
 ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, void* ws, size_t ws_bytes,
                        hipStream_t st);
+// The dense GEMM for few activation rows or few tiles (see ds3_gemm_skinny.hip), and whether launch_gemm
+// takes it for a shape when the caller names no configuration.  cus: compute units of the device.
+bool gemm_skinny_preferred(const GemmParams& p, int cus);
+ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
 // As launch_gemm with the library's own statically allocated workspace (one per device).
 ds3_status launch_gemm_static_scratch(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, hipStream_t st);
 size_t gemm_static_scratch_bytes();

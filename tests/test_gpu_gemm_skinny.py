@@ -1,0 +1,56 @@
+"""The GEMM for few rows or few tiles: shapes at the edges of its tiles and of its split of K (K-steps that
+do not divide among the wave groups, fewer K-steps than groups or stages), both scale modes and kinds, both
+output types.  Codes are small integers and scales powers of two, so every order of summation is exact and
+the FP32 output must equal the oracle bit for bit (BF16: its rounding)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ds3_oracle as orc
+from tests._gpu_util import announce, dev, host
+
+pytestmark = pytest.mark.gpu
+
+TABLE = np.array([0x00, 0x38, 0x40, 0xB8, 0xC0, 0x80], dtype=np.uint8)   # 0, 1, 2, -1, -2, -0
+
+SHAPES = [
+    (1, 1, 128), (1, 64, 256), (15, 31, 384), (16, 33, 640), (17, 96, 1152), (31, 32, 128), (32, 130, 2048),
+    (33, 129, 896), (63, 4100, 512), (64, 8200, 384), (65, 257, 128), (129, 1000, 1408), (64, 18433, 256),
+    (500, 2049, 384), (1000, 3001, 512), (2049, 65, 768), (1900, 1700, 128),
+]
+
+
+@pytest.mark.parametrize("pow2", [False, True])
+@pytest.mark.parametrize("per_row", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_skinny_exact(ds3, shape, per_row, pow2):
+    m, n, k = shape
+    rng = np.random.default_rng(m * 7 + n * 3 + k + per_row + 2 * pow2)
+    lda, ldb, ldc = k + 16 * int(rng.integers(0, 3)), k + 16 * int(rng.integers(0, 3)), (n + 3) // 4 * 4 + 8
+    announce(f"skinny {m}x{n}x{k} per_row={per_row} pow2={pow2} ld=({lda},{ldb},{ldc})")
+    a, b = TABLE[rng.integers(0, 6, (m, k))], TABLE[rng.integers(0, 6, (n, k))]
+    sa = np.ldexp(1.0, rng.integers(-2, 2, (m, k // 128))).astype(np.float32)
+    sb = np.ldexp(1.0, rng.integers(-1, 3, (n if per_row else (n + 127) // 128, k // 128))).astype(np.float32)
+    c0 = rng.integers(-8, 9, (m, n)).astype(np.float32)
+    ref = orc.gemm_fp8_bs(a, sa, b, sb, sb_per_row=per_row, c_in=None)
+
+    def padded(x, ld):
+        buf = torch.zeros((x.shape[0], ld), dtype=torch.uint8, device="cuda:0")
+        buf[:, :k] = dev(x)
+        return buf[:, :k]
+
+    fn = ds3.ds3_gemm_fp8_bs_pow2 if pow2 else ds3.ds3_gemm_fp8_bs
+    args = (padded(a, lda), dev(np.ascontiguousarray(sa.T)).t(), padded(b, ldb), dev(sb))
+    mode = ds3.DS3_BSCALE_PER_ROW if per_row else ds3.DS3_BSCALE_128x128
+    for accumulate in (False, True):
+        cbuf = torch.full((m, ldc), 7.0, dtype=torch.float32, device="cuda:0")
+        c = cbuf[:, :n]
+        c.copy_(dev(c0))
+        fn(*args, sb_mode=mode, c=c, accumulate=accumulate)
+        want = ref + c0 if accumulate else ref
+        assert np.array_equal(host(c).astype(np.float64), want), (shape, accumulate)
+        assert torch.all(cbuf[:, n:] == 7.0), "wrote beyond the row"
+    cbuf = torch.full((m + 1, ldc), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    fn(*args, sb_mode=mode, c=cbuf[:m, :n])
+    assert torch.equal(cbuf[:m, :n].cpu(), torch.from_numpy(ref).float().bfloat16())
+    assert torch.all(cbuf[:, n:] == 7.0) and torch.all(cbuf[m:] == 7.0), "wrote beyond the output"
