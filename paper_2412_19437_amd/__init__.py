@@ -4,18 +4,22 @@
 The functions here have the names of the C entry points declared in
 include/ds3.h and only marshal arguments: torch tensors supply device memory
 and the current stream, every step of the path runs in the library's kernels.
-There is no CPU fallback: importing this package without a built libds3.so
-raises.
+The calls that small layers are made of are marshalled natively (lib/ds3_native.so,
+csrc/ds3_binding.cpp), the others through ctypes.  There is no CPU fallback: using
+this package without the built libraries raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libds3.so")
+NATIVE_PATH = os.path.join(_HERE, "lib", "ds3_native.so")
 
 DS3_OK = 0
 DS3_F32, DS3_BF16 = 0, 1
@@ -112,6 +116,23 @@ def _L() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def _load_native():
+    """The extension module over the same library (loaded on first use, as the library is)."""
+    global _native
+    _L()
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2412_19437_amd.build`")
+    spec = importlib.util.spec_from_loader("ds3_native", importlib.machinery.ExtensionFileLoader("ds3_native", NATIVE_PATH))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.init(_check, _workspaces, gemm_workspace)
+    _native = module
+    return module
+
+
 def status_string(status: int) -> str:
     return _L().ds3_status_string(int(status)).decode()
 
@@ -130,7 +151,7 @@ def _dt(t: torch.Tensor) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _rows2d(t: torch.Tensor, name: str):
@@ -154,69 +175,38 @@ def _out(rows: int, cols: int, dtype, device) -> torch.Tensor:
 def _scales(rows: int, blocks: int, device, k_major: bool) -> torch.Tensor:
     """Logical [rows][blocks] FP32 tensor; k_major stores it as [blocks][rows]."""
     if k_major:
-        return torch.empty((blocks, rows), dtype=torch.float32, device=device).t()
+        return torch.empty_strided((rows, blocks), (1, max(rows, 1)), dtype=torch.float32, device=device)
     return torch.empty((rows, blocks), dtype=torch.float32, device=device)
-
-
-def _quant_act_1x128(entry: str, x: torch.Tensor, k_major_scales: bool):
-    m, k, ldx = _rows2d(x, "x")
-    q = _codes(m, k, x.device)
-    s = _scales(m, (k + 127) // 128, x.device, k_major_scales)
-    st = getattr(_L(), entry)(x.data_ptr(), _dt(x), m, k, ldx, q.data_ptr(), (k + 15) // 16 * 16,
-                              s.data_ptr(), s.stride(0), s.stride(1), _stream())
-    _check(st, entry)
-    return q, s
-
-
-def _quant_act_128x1(entry: str, x: torch.Tensor, k_major_scales: bool):
-    t, c, ldx = _rows2d(x, "x")
-    ldq = (t + 15) // 16 * 16
-    q_t = _codes(c, t, x.device)
-    s_t = _scales(c, (t + 127) // 128, x.device, k_major_scales)
-    st = getattr(_L(), entry)(x.data_ptr(), _dt(x), t, c, ldx, q_t.data_ptr(), ldq,
-                              s_t.data_ptr(), s_t.stride(0), s_t.stride(1), _stream())
-    _check(st, entry)
-    return q_t, s_t
-
-
-def _quant_w_128x128(entry: str, w: torch.Tensor):
-    n, k, ldw = _rows2d(w, "w")
-    q = _codes(n, k, w.device)
-    s = torch.empty(((n + 127) // 128, (k + 127) // 128), dtype=torch.float32, device=w.device)
-    st = getattr(_L(), entry)(w.data_ptr(), _dt(w), n, k, ldw, q.data_ptr(), (k + 15) // 16 * 16, s.data_ptr(),
-                              _stream())
-    _check(st, entry)
-    return q, s
 
 
 def ds3_quant_act_1x128(x: torch.Tensor, k_major_scales: bool = True):
     """x [M][K] FP32/BF16 -> (codes uint8 [M][K], scales FP32 logical [M][ceil(K/128)])."""
-    return _quant_act_1x128("ds3_quant_act_1x128", x, k_major_scales)
+    return (_native or _load_native()).quant_act_1x128(x, k_major_scales, False)
 
 
 def ds3_quant_act_1x128_pow2(x: torch.Tensor, k_major_scales: bool = True):
     """As ds3_quant_act_1x128 with power-of-two scales."""
-    return _quant_act_1x128("ds3_quant_act_1x128_pow2", x, k_major_scales)
+    return (_native or _load_native()).quant_act_1x128(x, k_major_scales, True)
 
 
 def ds3_quant_act_128x1(x: torch.Tensor, k_major_scales: bool = True):
     """x [T][C] -> (codes uint8 [C][T] token-contiguous, scales logical [C][ceil(T/128)])."""
-    return _quant_act_128x1("ds3_quant_act_128x1", x, k_major_scales)
+    return (_native or _load_native()).quant_act_128x1(x, k_major_scales, False)
 
 
 def ds3_quant_act_128x1_pow2(x: torch.Tensor, k_major_scales: bool = True):
     """As ds3_quant_act_128x1 with power-of-two scales."""
-    return _quant_act_128x1("ds3_quant_act_128x1_pow2", x, k_major_scales)
+    return (_native or _load_native()).quant_act_128x1(x, k_major_scales, True)
 
 
 def ds3_quant_w_128x128(w: torch.Tensor):
     """w [N][K] -> (codes uint8 [N][K], scales FP32 [ceil(N/128)][ceil(K/128)])."""
-    return _quant_w_128x128("ds3_quant_w_128x128", w)
+    return (_native or _load_native()).quant_w_128x128(w, False)
 
 
 def ds3_quant_w_128x128_pow2(w: torch.Tensor):
     """As ds3_quant_w_128x128 with power-of-two scales."""
-    return _quant_w_128x128("ds3_quant_w_128x128_pow2", w)
+    return (_native or _load_native()).quant_w_128x128(w, True)
 
 
 def ds3_gemm_fp8_bs(a, sa, b, sb, sb_mode: int = DS3_BSCALE_128x128, out_dtype=torch.bfloat16,
@@ -225,13 +215,20 @@ def ds3_gemm_fp8_bs(a, sa, b, sb, sb_mode: int = DS3_BSCALE_128x128, out_dtype=t
     [M][K/128]) and b [N][K] (scales sb: [ceil(N/128)][K/128], or [N][K/128]
     when sb_mode is DS3_BSCALE_PER_ROW).  workspace: "auto" (a cached tensor of the
     size the library asks for), None (never share tiles along K) or a uint8 tensor."""
-    return _gemm("ds3_gemm_fp8_bs_v", a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace)
+    return _gemm(a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace, False)
 
 
 def ds3_gemm_fp8_bs_pow2(a, sa, b, sb, sb_mode: int = DS3_BSCALE_128x128, out_dtype=torch.bfloat16,
                          c: torch.Tensor | None = None, accumulate: bool = False, variant: int = -1, workspace="auto"):
     """As ds3_gemm_fp8_bs for operands whose scales are all powers of two."""
-    return _gemm("ds3_gemm_fp8_bs_pow2", a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace)
+    return _gemm(a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace, True)
+
+
+def _gemm(a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace, pow2):
+    if c is None and out_dtype is not torch.bfloat16 and out_dtype is not torch.float32:
+        c = _out(a.shape[0], b.shape[0], out_dtype, a.device)      # (any name torch has for a type; the call checks it)
+    return (_native or _load_native()).gemm(a, sa, b, sb, sb_mode, out_dtype is torch.float32, c, int(accumulate), variant,
+                                            workspace, pow2)
 
 
 _workspaces: dict = {}
@@ -255,25 +252,6 @@ def new_gemm_workspace(nbytes: int, device) -> torch.Tensor:
     ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
     _check(_L().ds3_gemm_workspace_init(ws.data_ptr(), nbytes, _stream()), "ds3_gemm_workspace_init")
     return ws
-
-
-def _gemm(entry, a, sa, b, sb, sb_mode, out_dtype, c, accumulate, variant, workspace="auto"):
-    m, k, lda = _rows2d(a, "a")
-    n, kb_, ldb = _rows2d(b, "b")
-    if kb_ != k:
-        raise ValueError("a and b disagree on K")
-    if c is None:
-        c = _out(m, n, out_dtype, a.device)
-    _, _, ldc = _rows2d(c, "c")
-    if isinstance(workspace, str):                 # "auto": what the library asks for, from the cache
-        workspace = gemm_workspace(_L().ds3_gemm_workspace_bytes_v(variant, m, n, k, sb_mode), a.device)
-    st = getattr(_L(), entry)(variant, m, n, k, a.data_ptr(), lda, sa.data_ptr(), sa.stride(0), sa.stride(1),
-                              b.data_ptr(), ldb, sb.data_ptr(), sb.stride(0), sb.stride(1), sb_mode,
-                              c.data_ptr(), _dt(c), ldc, int(accumulate),
-                              workspace.data_ptr() if workspace is not None else None,
-                              workspace.numel() if workspace is not None else 0, _stream())
-    _check(st, entry)
-    return c
 
 
 def ds3_grouped_gemm_fp8_bs(a, sa, group_offsets, b, sb, out_dtype=torch.bfloat16,
@@ -325,63 +303,29 @@ def ds3_swiglu(h: torch.Tensor):
     return out
 
 
-def _quant_w_dual(entry: str, w: torch.Tensor):
-    n, k, ldw = _rows2d(w, "w")
-    q, q_t = _codes(n, k, w.device), _codes(k, n, w.device)
-    nb, kb = (n + 127) // 128, (k + 127) // 128
-    s = torch.empty((nb, kb), dtype=torch.float32, device=w.device)
-    s_t = torch.empty((kb, nb), dtype=torch.float32, device=w.device)
-    st = getattr(_L(), entry)(w.data_ptr(), _dt(w), n, k, ldw, q.data_ptr(), (k + 15) // 16 * 16, s.data_ptr(),
-                              q_t.data_ptr(), (n + 15) // 16 * 16, s_t.data_ptr(), _stream())
-    _check(st, entry)
-    return q, s, q_t, s_t
-
-
 def ds3_quant_w_128x128_dual(w: torch.Tensor):
     """w [N][K] -> (codes [N][K], scales [N/128][K/128], codes of the transpose [K][N], its scales [K/128][N/128])."""
-    return _quant_w_dual("ds3_quant_w_128x128_dual", w)
+    return (_native or _load_native()).quant_w_128x128_dual(w, False)
 
 
 def ds3_quant_w_128x128_dual_pow2(w: torch.Tensor):
     """As ds3_quant_w_128x128_dual with power-of-two scales."""
-    return _quant_w_dual("ds3_quant_w_128x128_dual_pow2", w)
-
-
-def _rmsnorm_quant(entry: str, x, gamma, eps, want_y, k_major_scales):
-    rows, cols, ldx = _rows2d(x, "x")
-    if x.dtype != torch.bfloat16 or gamma.dtype != torch.float32 or gamma.numel() != cols or not gamma.is_contiguous():
-        raise TypeError("x must be BF16 and gamma a contiguous FP32 vector of x's width")
-    q = _codes(rows, cols, x.device)
-    s = _scales(rows, (cols + 127) // 128, x.device, k_major_scales)
-    y = torch.empty((rows, cols), dtype=torch.bfloat16, device=x.device) if want_y else None
-    st = getattr(_L(), entry)(x.data_ptr(), rows, cols, ldx, gamma.data_ptr(), float(eps),
-                              y.data_ptr() if want_y else None, cols, q.data_ptr(), (cols + 15) // 16 * 16,
-                              s.data_ptr(), s.stride(0), s.stride(1), _stream())
-    _check(st, entry)
-    return (q, s, y) if want_y else (q, s)
+    return (_native or _load_native()).quant_w_128x128_dual(w, True)
 
 
 def ds3_rmsnorm_quant_1x128(x, gamma, eps: float = 1e-6, want_y: bool = False, k_major_scales: bool = True):
     """RMSNorm(x) * gamma rounded to BF16, 1x128-quantized: (codes, scales[, the BF16 activation])."""
-    return _rmsnorm_quant("ds3_rmsnorm_quant_1x128", x, gamma, eps, want_y, k_major_scales)
+    return (_native or _load_native()).rmsnorm_quant_1x128(x, gamma, eps, want_y, k_major_scales, False)
 
 
 def ds3_rmsnorm_quant_1x128_pow2(x, gamma, eps: float = 1e-6, want_y: bool = False, k_major_scales: bool = True):
     """As ds3_rmsnorm_quant_1x128 with power-of-two scales."""
-    return _rmsnorm_quant("ds3_rmsnorm_quant_1x128_pow2", x, gamma, eps, want_y, k_major_scales)
+    return (_native or _load_native()).rmsnorm_quant_1x128(x, gamma, eps, want_y, k_major_scales, True)
 
 
 def ds3_quant_act_1x128_e5m6(x: torch.Tensor, k_major_scales: bool = True):
     """x [M][K] BF16 -> (packed E5M6 codes uint8 [M][3K/2], power-of-two scales logical [M][ceil(K/128)])."""
-    m, k, ldx = _rows2d(x, "x")
-    if x.dtype != torch.bfloat16:
-        raise TypeError("x must be BF16")
-    q = torch.empty((m, k * 3 // 2), dtype=torch.uint8, device=x.device)
-    s = _scales(m, (k + 127) // 128, x.device, k_major_scales)
-    st = _L().ds3_quant_act_1x128_e5m6(x.data_ptr(), m, k, ldx, q.data_ptr(), k * 3 // 2, s.data_ptr(), s.stride(0),
-                                      s.stride(1), _stream())
-    _check(st, "ds3_quant_act_1x128_e5m6")
-    return q, s
+    return (_native or _load_native()).quant_act_1x128_e5m6(x, k_major_scales)
 
 
 def ds3_dequant_e5m6(q: torch.Tensor, s: torch.Tensor):
@@ -411,27 +355,14 @@ def ds3_adamw_bf16_states(master_w, grad, m, v, lr, beta1, beta2, eps, weight_de
     _check(st, "ds3_adamw_bf16_states")
 
 
-def _swiglu_quant(entry: str, h: torch.Tensor, k_major_scales: bool):
-    rows, two_i, ldh = _rows2d(h, "h")
-    if h.dtype != torch.bfloat16 or two_i % 2:
-        raise TypeError("h must be BF16 with an even number of columns")
-    inter = two_i // 2
-    q = _codes(rows, inter, h.device)
-    s = _scales(rows, (inter + 127) // 128, h.device, k_major_scales)
-    st = getattr(_L(), entry)(h.data_ptr(), rows, inter, ldh, q.data_ptr(), (inter + 15) // 16 * 16,
-                              s.data_ptr(), s.stride(0), s.stride(1), _stream())
-    _check(st, entry)
-    return q, s
-
-
 def ds3_swiglu_quant_1x128(h: torch.Tensor, k_major_scales: bool = True):
     """h [rows][2*inter] BF16 (gate | up) -> 1x128-quantized silu(gate) * up: (codes [rows][inter], scales)."""
-    return _swiglu_quant("ds3_swiglu_quant_1x128", h, k_major_scales)
+    return (_native or _load_native()).swiglu_quant_1x128(h, k_major_scales, False)
 
 
 def ds3_swiglu_quant_1x128_pow2(h: torch.Tensor, k_major_scales: bool = True):
     """As ds3_swiglu_quant_1x128 with power-of-two scales."""
-    return _swiglu_quant("ds3_swiglu_quant_1x128_pow2", h, k_major_scales)
+    return (_native or _load_native()).swiglu_quant_1x128(h, k_major_scales, True)
 
 
 def _grouped_swiglu_quant(entry, a, sa, group_offsets, b, sb, k_major_scales, workspace="auto"):
@@ -465,26 +396,14 @@ def ds3_grouped_gemm_swiglu_quant_fp8_bs_pow2(a, sa, group_offsets, b, sb, k_maj
                                  workspace)
 
 
-def _retile(entry: str, q: torch.Tensor, s: torch.Tensor, k_major_scales: bool):
-    t, c, ldq = _rows2d(q, "q")
-    if q.dtype != torch.uint8 or s.dtype != torch.float32 or tuple(s.shape) != (t, (c + 127) // 128):
-        raise ValueError("q: uint8 [T][C]; s: float32 logical [T][ceil(C/128)]")
-    q_t = _codes(c, t, q.device)
-    s_t = _scales(c, (t + 127) // 128, q.device, k_major_scales)
-    st = getattr(_L(), entry)(q.data_ptr(), t, c, ldq, s.data_ptr(), s.stride(0), s.stride(1), q_t.data_ptr(),
-                              (t + 15) // 16 * 16, s_t.data_ptr(), s_t.stride(0), s_t.stride(1), _stream())
-    _check(st, entry)
-    return q_t, s_t
-
-
 def ds3_retile_1x128_to_128x1(q: torch.Tensor, s: torch.Tensor, k_major_scales: bool = True):
     """1x128-quantized [T][C] (codes, scales) -> 128x1-quantized, transposed: (codes [C][T], scales [C][ceil(T/128)])."""
-    return _retile("ds3_retile_1x128_to_128x1", q, s, k_major_scales)
+    return (_native or _load_native()).retile(q, s, k_major_scales, False)
 
 
 def ds3_retile_1x128_to_128x1_pow2(q: torch.Tensor, s: torch.Tensor, k_major_scales: bool = True):
     """As ds3_retile_1x128_to_128x1 with power-of-two output scales."""
-    return _retile("ds3_retile_1x128_to_128x1_pow2", q, s, k_major_scales)
+    return (_native or _load_native()).retile(q, s, k_major_scales, True)
 
 
 def ds3_gemm_num_variants() -> int:

@@ -10,6 +10,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -50,6 +51,23 @@ def _compile(src: str, objdir: str) -> str:
     return obj
 
 
+def _compile_binding() -> str:
+    """ds3_native.so: the Python functions' native marshalling, a host-only extension module against torch's C++ API."""
+    import torch
+    from torch.utils import cpp_extension
+    inc = [*cpp_extension.include_paths("cuda"), sysconfig.get_paths()["include"]]
+    out = os.path.join(LIBDIR, "ds3_native.so")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-isystem{d}" for d in inc),
+           os.path.join(CSRC, "ds3_binding.cpp"), "-o", out, f"-L{LIBDIR}", "-lds3",
+           f"-L{os.path.join(os.path.dirname(torch.__file__), 'lib')}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on ds3_binding.cpp:\n" + r.stderr)
+    return out
+
+
 def build_library(verbose: bool = True) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -60,6 +78,7 @@ def build_library(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _compile_binding()
     if verbose:
         print("built", LIB)
     return LIB
