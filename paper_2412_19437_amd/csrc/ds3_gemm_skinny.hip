@@ -15,6 +15,7 @@
 // M x N x K): 32x18432x7168 52 -> 31 (2.8 -> 4.3 TB/s of weights), 32x4096x7168
 // 33 -> 12, 256x512x1024 9.4 -> 3.4, 512x2048x2048 12.9 -> 8.0, 1024x1024x4096
 // 19.6 -> 11.6; per-row scales, FP32 output: 512x1024x4096 19.9 -> 9.0.
+// Experts' groups of few rows take the same kernel (`launch_grouped` below).
 // What is left at 32 rows is the ramp and the drain of one round of tiles; the
 // smallest calls are a launch and one latency per stage.
 #include "ds3_dev.h"
@@ -43,8 +44,13 @@ struct SkinnyCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-template <class C, bool ROWSB, bool OUT_BF16, bool POW2>
+// GROUPED: experts' groups of rows, each against its own weights; SWIQ: with SwiGLU and the 1x128 quantizer of the
+// next Linear's input on the tile (gate and up rows interleaved in blocks of 128, as in ds3_gemm.hip).  Both with
+// WK == 1: every output element is then the main kernel's sequence of operations, bit for bit.
+template <class C, bool ROWSB, bool OUT_BF16, bool POW2, bool GROUPED = false, bool SWIQ = false>
 __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) {
+    static_assert(!GROUPED || (C::WK == 1 && !ROWSB), "grouped: one wave group, block scales");
+    static_assert(!SWIQ || (GROUPED && C::BN == 256), "a gate and an up block per tile");
     constexpr int FN = C::FN, FM = C::FM, WN = C::WN, WK = C::WK, NS = C::NS, BN = C::BN, BM = C::BM;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[C::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -55,18 +61,64 @@ __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) 
 
     // ---- which tile: the tile list is cut into one contiguous chunk per XCD (workgroups are dealt
     // round robin to them), row tiles innermost, so that those which share weights share an L2
-    const int ntiles = p.tiles_m * p.tiles_n, per_xcd = (ntiles + 7) >> 3;
+    int tiles_m = p.tiles_m;                           // grouped: the host's upper bound
+    [[maybe_unused]] auto group_row = [&](int g) { return min(p.group_offsets[min(g, p.G)], p.M); };
+    [[maybe_unused]] auto tiles_before = [&](int g0, int& mine) -> int {   // row tiles of experts g0 .. g0 + lane; `mine`: of the last of them
+        const int g = g0 + lane;
+        mine = g < p.G ? max(0, group_row(g + 1) - group_row(g) + BM - 1) / BM : 0;
+        int sum = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(sum, d);
+            if (lane >= d) sum += o;
+        }
+        return sum;
+    };
+    [[maybe_unused]] int cum = 0, own = 0;             // of the first 64 experts, kept: most calls have no more
+    if constexpr (GROUPED) {
+        cum = tiles_before(0, own);
+        tiles_m = __builtin_amdgcn_readlane(cum, 63);
+        for (int g0 = 64; g0 < p.G; g0 += 64) {
+            int unused;
+            tiles_m += __builtin_amdgcn_readlane(tiles_before(g0, unused), 63);
+        }
+    }
+    const int ntiles = tiles_m * p.tiles_n, per_xcd = (ntiles + 7) >> 3;
     const int local = (int)(blockIdx.x >> 3), t = (int)(blockIdx.x & 7) * per_xcd + local;
     if (local >= per_xcd || t >= ntiles) return;
-    const int n0 = t / p.tiles_m * BN, m0 = t % p.tiles_m * BM;
-    const int m_rows = min(p.M - m0, BM);
+    int n0, m0, m_end, grp = 0;
+    if constexpr (GROUPED) {
+        // the expert whose tiles [before * tiles_n, (before + its row tiles) * tiles_n) hold t
+        int before = 0, g0 = 0;
+        for (;;) {
+            const unsigned long long past = __ballot((before + cum) * p.tiles_n > t);
+            if (past != 0) {
+                const int l = __builtin_ctzll(past);
+                const int nt_g = __builtin_amdgcn_readlane(own, l);
+                before += __builtin_amdgcn_readlane(cum, l) - nt_g;
+                grp = g0 + l;
+                const int r = t - before * p.tiles_n;  // its column tiles, the row tiles innermost
+                n0 = r / nt_g * BN;
+                m0 = __builtin_amdgcn_readfirstlane(group_row(grp)) + r % nt_g * BM;
+                m_end = __builtin_amdgcn_readfirstlane(group_row(grp + 1));
+                break;
+            }
+            before += __builtin_amdgcn_readlane(cum, 63);
+            g0 += 64;
+            if (g0 >= p.G) return;                     // (not reached: t is below the sum over all experts)
+            cum = tiles_before(g0, own);
+        }
+    } else {
+        n0 = t / p.tiles_m * BN; m0 = t % p.tiles_m * BM; m_end = p.M;
+    }
+    const int m_rows = min(m_end - m0, BM);
     const int n_rows = min(p.N - n0, BN);
 
     // Descriptors over the tile's valid bytes: rows beyond them move no data.
     const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(p.a + (int64_t)m0 * p.lda), 0, (int)((int64_t)(m_rows - 1) * p.lda + p.K), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(p.b + (int64_t)n0 * p.ldb), 0,
+        (void*)(p.b + (GROUPED ? (int64_t)grp * p.b_group_stride : 0) + (int64_t)n0 * p.ldb), 0,
         (int)((int64_t)(n_rows - 1) * p.ldb + p.K), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_sa = __builtin_amdgcn_make_buffer_rsrc((void*)p.sa, 0, 0x7ffffffc, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_sb = __builtin_amdgcn_make_buffer_rsrc((void*)p.sb, 0, 0x7ffffffc, 0x00020000);
@@ -83,7 +135,7 @@ __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) 
 #pragma unroll
     for (int h = 0; h < C::NSA; ++h) soff_a[h] = (unsigned)((m0 + min(h * 64 + lane, m_rows - 1)) * (int)p.sar) * 4u;
     const int sb_row = ROWSB ? n0 + min(wn * FN * 16 + lane, n_rows - 1) : min((n0 + wn * FN * 16) >> 7, ((p.N + 127) >> 7) - 1);
-    unsigned soff_b = (unsigned)(sb_row * (int)p.sbr) * 4u;
+    unsigned soff_b = (unsigned)((GROUPED ? grp * (int)p.sb_group_stride : 0) + sb_row * (int)p.sbr) * 4u;
     unsigned sa_step = (unsigned)p.sak * 4u, sb_step = (unsigned)p.sbk * 4u;   // read once, not from the kernel arguments in the loop
     asm volatile("" : "+v"(soff_b), "+s"(sa_step), "+s"(sb_step));
 
@@ -202,6 +254,28 @@ __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) 
         }
         return v;
     };
+    if constexpr (SWIQ) {
+        // 16 lanes a row, eight output columns each: the main kernel's epilogue, expression for expression
+        const int64_t ob = n0 >> 8;                    // 1x128 tile of the output
+        for (int row = tid >> 4; row < m_rows; row += C::NT / 16) {
+            const float* hr = red + row * C::RLD + l16 * 8;
+            unsigned int w[4], m = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned int g = pack_bf16x2(hr[2 * e], hr[2 * e + 1]), u = pack_bf16x2(hr[128 + 2 * e], hr[128 + 2 * e + 1]);
+                w[e] = pack_bf16x2(silu_mul(bf16_lo(g), bf16_lo(u)), silu_mul(bf16_hi(g), bf16_hi(u)));
+                m = umax(m, umax(w[e] & 0x7fff0000u, (w[e] << 16) & 0x7fff0000u));
+            }
+            m = row16_max_bits(m);
+            const GroupScale gs = group_scale(as_f32(m), p.q_pow2);
+            const int64_t grow = m0 + row;
+            *reinterpret_cast<u32x2*>(p.q_out + grow * p.ldq + ob * 128 + l16 * 8) =
+                u32x2{cvt4_e4m3(bf16_lo(w[0]) * gs.r, bf16_hi(w[0]) * gs.r, bf16_lo(w[1]) * gs.r, bf16_hi(w[1]) * gs.r),
+                      cvt4_e4m3(bf16_lo(w[2]) * gs.r, bf16_hi(w[2]) * gs.r, bf16_lo(w[3]) * gs.r, bf16_hi(w[3]) * gs.r)};
+            if (l16 == 0) p.s_out[grow * p.sor + ob * p.sok] = gs.s;
+        }
+        return;
+    }
     for (int idx = tid; idx < m_rows * (BN / 4); idx += C::NT) {
         const int row = idx / (BN / 4), col = idx % (BN / 4) * 4;
         if (col >= n_rows) continue;
@@ -296,6 +370,55 @@ ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
         case 3: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
         default: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
     }
+}
+
+// ---- grouped ----------------------------------------------------------------------
+template <class C, bool SWIQ>
+static ds3_status launch_grouped(GemmParams p, ds3_dtype ct, bool pow2, hipStream_t st) {
+    p.tiles_m = (p.M + C::BM - 1) / C::BM + p.G;        // an upper bound; workgroups beyond the true count leave at once
+    if (p.tiles_m > p.M) p.tiles_m = p.M;               // (a row tile has a row)
+    p.tiles_n = (p.N + C::BN - 1) / C::BN;
+    const dim3 grid((unsigned)(((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8)), block(C::NT);
+    (void)hipGetLastError();                            // a stale error of earlier, unrelated work is not this launch's
+    if constexpr (SWIQ) {
+        if (pow2) gemm_skinny_kernel<C, false, true, true, true, true><<<grid, block, 0, st>>>(p);
+        else gemm_skinny_kernel<C, false, true, false, true, true><<<grid, block, 0, st>>>(p);
+    } else if (ct == DS3_BF16) {
+        if (pow2) gemm_skinny_kernel<C, false, true, true, true><<<grid, block, 0, st>>>(p);
+        else gemm_skinny_kernel<C, false, true, false, true><<<grid, block, 0, st>>>(p);
+    } else {
+        if (pow2) gemm_skinny_kernel<C, false, false, true, true><<<grid, block, 0, st>>>(p);
+        else gemm_skinny_kernel<C, false, false, false, true><<<grid, block, 0, st>>>(p);
+    }
+    return hipGetLastError() == hipSuccess ? DS3_OK : DS3_ERR_LAUNCH;
+}
+
+// Few rows an expert: 32-row tiles up to a mean of 16 rows, 64-row tiles up to 32 (loads spread about their
+// mean; a second row tile of an expert costs more than the padding).  Weights from HBM, gate|up + down, us, main
+// kernel / 32-row / 64-row tiles, H 7168, I 2048: 32 experts of 4 rows 252 / 239 / 240, of 16 rows 256 / 245 / 246,
+// of 32 rows 261 / 278 / 255, of 64 rows 270 / 376 / 302; 8 experts of 4 rows 80 / 72 / 74; H 2048, I 1024, 32
+// experts of 4 rows 51 / 40 / 42, of 32 rows 52 / 53 / 45, of 64 rows 54 / 68 / 58.  Large calls run at the rate
+// the weights come from HBM (6.0 TB/s), small ones were short of bytes in flight.
+static int grouped_rows(const GemmParams& p) {
+    return (int64_t)p.M <= (int64_t)16 * p.G ? 32 : ((int64_t)p.M <= (int64_t)32 * p.G ? 64 : 0);
+}
+
+bool grouped_skinny_preferred(const GemmParams& p) {
+    if (grouped_rows(p) == 0) return false;
+    // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel
+    return (int64_t)257 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) &&
+           ((int64_t)p.M / 32 + p.G + 1) * ((int64_t)p.N / 128 + 1) < (1 << 28);
+}
+
+// Gate|up: 256 weight rows a workgroup, one per compute unit and as many stages as LDS holds; a plain product: 128
+// weight rows, two workgroups per compute unit, so that one's start and end are hidden behind the other (its K is
+// the short one: 256 rows and four stages take 88 us where these take 82).
+ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, bool pow2, hipStream_t st) {
+    if (grouped_rows(p) == 32)
+        return swiglu_quant ? launch_grouped<SkinnyCfg<4, 2, 4, 1, 4>, true>(p, ct, pow2, st)
+                            : launch_grouped<SkinnyCfg<2, 2, 4, 1, 3>, false>(p, ct, pow2, st);
+    return swiglu_quant ? launch_grouped<SkinnyCfg<2, 4, 8, 1, 3>, true>(p, ct, pow2, st)
+                        : launch_grouped<SkinnyCfg<2, 4, 4, 1, 3>, false>(p, ct, pow2, st);
 }
 
 }  // namespace ds3

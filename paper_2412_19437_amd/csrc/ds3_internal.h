@@ -75,6 +75,9 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
 // takes it for a shape when the caller names no configuration.  cus: compute units of the device.
 bool gemm_skinny_preferred(const GemmParams& p, int cus);
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
+// The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it.
+bool grouped_skinny_preferred(const GemmParams& p);
+ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, bool pow2, hipStream_t st);
 // As launch_gemm with the library's own statically allocated workspace (one per device).
 ds3_status launch_gemm_static_scratch(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, hipStream_t st);
 size_t gemm_static_scratch_bytes();
