@@ -85,13 +85,19 @@ at::Tensor gemm_out(int64_t rows, int64_t cols, at::ScalarType type, const at::T
 template <typename T = uint8_t> T* ptr(const at::Tensor& t) { return static_cast<T*>(t.data_ptr()); }
 void* stream() { return c10::hip::getCurrentHIPStream(-1).stream(); }
 
-// The C call without the interpreter lock; a status other than DS3_OK is raised by the package.
-template <typename F> void call(const char* where, F&& f) {
+// The interpreter lock is released while one of these exists, and taken again however its scope is left.
+struct Unlocked {
+    PyThreadState* const save = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(save); }
+};
+
+// The C call without the interpreter lock; a status other than DS3_OK is raised by the package.  What the call
+// is given (a tensor's pointer and strides may throw) is worked out by the caller, under the lock.
+template <typename F, typename... A> void call(const char* where, F* fn, A... args) {
     ds3_status st;
     {
-        PyThreadState* const save = PyEval_SaveThread();
-        st = f();
-        PyEval_RestoreThread(save);
+        const Unlocked unlocked;
+        st = fn(args...);
     }
     if (st == DS3_OK) return;
     PyObject* r = PyObject_CallFunction(g_check, "is", (int)st, where);
@@ -151,10 +157,8 @@ PyObject* quant_act_1x128(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const at::Tensor q = codes(m.rows, m.cols, x), s = scales(m.rows, blocks(m.cols), km, x);
     const ds3_dtype t = dtype_of(x);
     void* st = stream();
-    call(p2 ? "ds3_quant_act_1x128_pow2" : "ds3_quant_act_1x128", [&] {
-        return (p2 ? ds3_quant_act_1x128_pow2 : ds3_quant_act_1x128)(ptr(x), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16),
-                                                                      ptr<float>(s), s.stride(0), s.stride(1), st);
-    });
+    call(p2 ? "ds3_quant_act_1x128_pow2" : "ds3_quant_act_1x128", p2 ? ds3_quant_act_1x128_pow2 : ds3_quant_act_1x128,
+         ptr(x), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16), ptr<float>(s), s.stride(0), s.stride(1), st);
     return pair(q, s);
     END_HANDLE_TH_ERRORS
 }
@@ -169,10 +173,8 @@ PyObject* quant_act_128x1(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const at::Tensor q = codes(m.cols, m.rows, x), s = scales(m.cols, blocks(m.rows), km, x);
     const ds3_dtype t = dtype_of(x);
     void* st = stream();
-    call(p2 ? "ds3_quant_act_128x1_pow2" : "ds3_quant_act_128x1", [&] {
-        return (p2 ? ds3_quant_act_128x1_pow2 : ds3_quant_act_128x1)(ptr(x), t, m.rows, m.cols, m.ld, ptr(q), up(m.rows, 16),
-                                                                      ptr<float>(s), s.stride(0), s.stride(1), st);
-    });
+    call(p2 ? "ds3_quant_act_128x1_pow2" : "ds3_quant_act_128x1", p2 ? ds3_quant_act_128x1_pow2 : ds3_quant_act_128x1,
+         ptr(x), t, m.rows, m.cols, m.ld, ptr(q), up(m.rows, 16), ptr<float>(s), s.stride(0), s.stride(1), st);
     return pair(q, s);
     END_HANDLE_TH_ERRORS
 }
@@ -187,10 +189,8 @@ PyObject* quant_w_128x128(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const at::Tensor q = codes(m.rows, m.cols, w), s = scales(blocks(m.rows), blocks(m.cols), false, w);
     const ds3_dtype t = dtype_of(w);
     void* st = stream();
-    call(p2 ? "ds3_quant_w_128x128_pow2" : "ds3_quant_w_128x128", [&] {
-        return (p2 ? ds3_quant_w_128x128_pow2 : ds3_quant_w_128x128)(ptr(w), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16),
-                                                                      ptr<float>(s), st);
-    });
+    call(p2 ? "ds3_quant_w_128x128_pow2" : "ds3_quant_w_128x128", p2 ? ds3_quant_w_128x128_pow2 : ds3_quant_w_128x128,
+         ptr(w), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16), ptr<float>(s), st);
     return pair(q, s);
     END_HANDLE_TH_ERRORS
 }
@@ -206,10 +206,9 @@ PyObject* quant_w_128x128_dual(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const at::Tensor s = scales(blocks(m.rows), blocks(m.cols), false, w), s_t = scales(blocks(m.cols), blocks(m.rows), false, w);
     const ds3_dtype t = dtype_of(w);
     void* st = stream();
-    call(p2 ? "ds3_quant_w_128x128_dual_pow2" : "ds3_quant_w_128x128_dual", [&] {
-        return (p2 ? ds3_quant_w_128x128_dual_pow2 : ds3_quant_w_128x128_dual)(ptr(w), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16),
-                                                                                ptr<float>(s), ptr(qt), up(m.rows, 16), ptr<float>(s_t), st);
-    });
+    call(p2 ? "ds3_quant_w_128x128_dual_pow2" : "ds3_quant_w_128x128_dual",
+         p2 ? ds3_quant_w_128x128_dual_pow2 : ds3_quant_w_128x128_dual,
+         ptr(w), t, m.rows, m.cols, m.ld, ptr(q), up(m.cols, 16), ptr<float>(s), ptr(qt), up(m.rows, 16), ptr<float>(s_t), st);
     PyObject* a = pair(q, s);
     PyObject* b = a ? pair(qt, s_t) : nullptr;
     PyObject* r = b ? PySequence_Concat(a, b) : nullptr;
@@ -230,10 +229,8 @@ PyObject* swiglu_quant_1x128(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const int64_t inter = m.cols / 2;
     const at::Tensor q = codes(m.rows, inter, h), s = scales(m.rows, blocks(inter), km, h);
     void* st = stream();
-    call(p2 ? "ds3_swiglu_quant_1x128_pow2" : "ds3_swiglu_quant_1x128", [&] {
-        return (p2 ? ds3_swiglu_quant_1x128_pow2 : ds3_swiglu_quant_1x128)(ptr(h), m.rows, inter, m.ld, ptr(q), up(inter, 16),
-                                                                            ptr<float>(s), s.stride(0), s.stride(1), st);
-    });
+    call(p2 ? "ds3_swiglu_quant_1x128_pow2" : "ds3_swiglu_quant_1x128", p2 ? ds3_swiglu_quant_1x128_pow2 : ds3_swiglu_quant_1x128,
+         ptr(h), m.rows, inter, m.ld, ptr(q), up(inter, 16), ptr<float>(s), s.stride(0), s.stride(1), st);
     return pair(q, s);
     END_HANDLE_TH_ERRORS
 }
@@ -252,11 +249,10 @@ PyObject* rmsnorm_quant_1x128(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const at::Tensor q = codes(m.rows, m.cols, x), s = scales(m.rows, blocks(m.cols), km, x);
     const at::Tensor y = want_y ? empty2d(m.rows, m.cols, m.cols, at::kBFloat16, x) : at::Tensor();
     void* st = stream();
-    call(p2 ? "ds3_rmsnorm_quant_1x128_pow2" : "ds3_rmsnorm_quant_1x128", [&] {
-        return (p2 ? ds3_rmsnorm_quant_1x128_pow2 : ds3_rmsnorm_quant_1x128)(
-            ptr(x), m.rows, m.cols, m.ld, ptr<float>(gamma), (float)eps, want_y ? y.data_ptr() : nullptr, m.cols, ptr(q),
-            up(m.cols, 16), ptr<float>(s), s.stride(0), s.stride(1), st);
-    });
+    call(p2 ? "ds3_rmsnorm_quant_1x128_pow2" : "ds3_rmsnorm_quant_1x128",
+         p2 ? ds3_rmsnorm_quant_1x128_pow2 : ds3_rmsnorm_quant_1x128,
+         ptr(x), m.rows, m.cols, m.ld, ptr<float>(gamma), (float)eps, want_y ? y.data_ptr() : nullptr, m.cols, ptr(q),
+         up(m.cols, 16), ptr<float>(s), s.stride(0), s.stride(1), st);
     PyObject* r = pair(q, s);
     if (!r || !want_y) return r;
     PyObject* yo = THPVariable_Wrap(y);
@@ -280,11 +276,10 @@ PyObject* retile(PyObject*, PyObject* const* o, Py_ssize_t n) {
         fail(PyExc_ValueError, "q: uint8 [T][C]; s: float32 logical [T][ceil(C/128)]");
     const at::Tensor qt = codes(m.cols, m.rows, q), s_t = scales(m.cols, blocks(m.rows), km, q);
     void* st = stream();
-    call(p2 ? "ds3_retile_1x128_to_128x1_pow2" : "ds3_retile_1x128_to_128x1", [&] {
-        return (p2 ? ds3_retile_1x128_to_128x1_pow2 : ds3_retile_1x128_to_128x1)(
-            ptr(q), m.rows, m.cols, m.ld, ptr<float>(s), s.stride(0), s.stride(1), ptr(qt), up(m.rows, 16), ptr<float>(s_t),
-            s_t.stride(0), s_t.stride(1), st);
-    });
+    call(p2 ? "ds3_retile_1x128_to_128x1_pow2" : "ds3_retile_1x128_to_128x1",
+         p2 ? ds3_retile_1x128_to_128x1_pow2 : ds3_retile_1x128_to_128x1,
+         ptr(q), m.rows, m.cols, m.ld, ptr<float>(s), s.stride(0), s.stride(1), ptr(qt), up(m.rows, 16), ptr<float>(s_t),
+         s_t.stride(0), s_t.stride(1), st);
     return pair(qt, s_t);
     END_HANDLE_TH_ERRORS
 }
@@ -300,9 +295,8 @@ PyObject* quant_act_1x128_e5m6(PyObject*, PyObject* const* o, Py_ssize_t n) {
     const int64_t width = m.cols * 3 / 2;
     const at::Tensor q = empty2d(m.rows, width, width, at::kByte, x), s = scales(m.rows, blocks(m.cols), km, x);
     void* st = stream();
-    call("ds3_quant_act_1x128_e5m6", [&] {
-        return ds3_quant_act_1x128_e5m6(ptr(x), m.rows, m.cols, m.ld, ptr(q), width, ptr<float>(s), s.stride(0), s.stride(1), st);
-    });
+    call("ds3_quant_act_1x128_e5m6", ds3_quant_act_1x128_e5m6,
+         ptr(x), m.rows, m.cols, m.ld, ptr(q), width, ptr<float>(s), s.stride(0), s.stride(1), st);
     return pair(q, s);
     END_HANDLE_TH_ERRORS
 }
@@ -318,16 +312,15 @@ PyObject* gemm(PyObject*, PyObject* const* o, Py_ssize_t n) {
     if (ma.cols != mb.cols) fail(PyExc_ValueError, "a and b disagree on K");
     at::Tensor c = o[6] == Py_None ? gemm_out(ma.rows, mb.rows, f32 ? at::kFloat : at::kBFloat16, a) : tensor(o[6]);
     const Mat mc = rows2d(c, "c");
+    const int64_t sar = sa.stride(0), sak = sa.stride(1), sbr = sb.stride(0), sbk = sb.stride(1);     // (fewer than two: an IndexError)
     void* st = stream();
     const size_t bytes = PyUnicode_Check(o[9])
                              ? ds3_gemm_workspace_bytes_v((int)variant, ma.rows, mb.rows, ma.cols, (ds3_bscale)sb_mode) : 0;
     const Workspace w = workspace_of(o[9], bytes, o[0], a, st);
     const ds3_dtype ct = dtype_of(c);
-    call(p2 ? "ds3_gemm_fp8_bs_pow2" : "ds3_gemm_fp8_bs_v", [&] {
-        return (p2 ? ds3_gemm_fp8_bs_pow2 : ds3_gemm_fp8_bs_v)(
-            (int)variant, ma.rows, mb.rows, ma.cols, ptr(a), ma.ld, ptr<float>(sa), sa.stride(0), sa.stride(1), ptr(b), mb.ld,
-            ptr<float>(sb), sb.stride(0), sb.stride(1), (ds3_bscale)sb_mode, c.data_ptr(), ct, mc.ld, (int)accumulate, w.p, w.n, st);
-    });
+    call(p2 ? "ds3_gemm_fp8_bs_pow2" : "ds3_gemm_fp8_bs_v", p2 ? ds3_gemm_fp8_bs_pow2 : ds3_gemm_fp8_bs_v,
+         (int)variant, ma.rows, mb.rows, ma.cols, ptr(a), ma.ld, ptr<float>(sa), sar, sak, ptr(b), mb.ld,
+         ptr<float>(sb), sbr, sbk, (ds3_bscale)sb_mode, c.data_ptr(), ct, mc.ld, (int)accumulate, w.p, w.n, st);
     if (o[6] == Py_None) return THPVariable_Wrap(c);
     Py_INCREF(o[6]);
     return o[6];

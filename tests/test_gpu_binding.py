@@ -22,6 +22,13 @@ def test_refusals(ds3):
     with pytest.raises(ds3.Ds3Error) as e:
         ds3.ds3_gemm_fp8_bs(q[:, 1:129], s, w[:, 1:129], sw)
     assert e.value.status == 3 and "ds3_gemm_fp8_bs_v" in str(e.value)
+    for bad in (s[:, 0], s[0, 0]):                        # scales without two strides
+        with pytest.raises(IndexError):
+            ds3.ds3_gemm_fp8_bs(q, bad, w, sw)
+        with pytest.raises(IndexError):
+            ds3.ds3_gemm_fp8_bs(q, s, w, bad)
+    with pytest.raises(RuntimeError):                     # no memory of its own behind the tensor: its pointer throws
+        torch.vmap(lambda t: ds3.ds3_quant_act_1x128(t)[0])(x[None])
     with pytest.raises(ds3.Ds3Error):                     # a workspace below the counters' size
         ds3.ds3_gemm_fp8_bs(q, s, w, sw, workspace=torch.zeros(16, dtype=torch.uint8, device="cuda:0"))
 
