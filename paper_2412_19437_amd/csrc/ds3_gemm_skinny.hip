@@ -357,8 +357,9 @@ static int skinny_choice(int M, int N, int K, int cus) {
 bool gemm_skinny_preferred(const GemmParams& p, int cus) {
     const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
     if (p.M > 64 && tiles >= cus) return false;
-    // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel
-    return (int64_t)129 * p.ldb + p.K < (1ll << 31) && (int64_t)65 * p.lda + p.K < (1ll << 31) && p.N < (1 << 26);
+    // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel; so do leading dimensions
+    // that it refuses (its 128-row tiles reach further than these), for every size alike
+    return (int64_t)129 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) && p.N < (1 << 26);
 }
 
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st) {

@@ -72,6 +72,8 @@ def test_gemm_rejects_bad_arguments_on_the_host(pkg):
     assert call(ldc=18) == 3
     assert call(ct=1, acc=1) == 4                 # accumulate into BF16
     assert call(mode=5) == 4
+    for rows in (16, 64, 200):                    # leading dimensions beyond a tile's 32-bit offsets, however few the rows
+        assert call(M=rows, lda=1 << 24) == 5 and call(M=rows, ldb=1 << 24) == 5
     assert call(M=0, a=None, c=None) == 0         # empty
     assert call(M=-1) == 2
     gg = L.ds3_grouped_gemm_fp8_bs
