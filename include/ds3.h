@@ -298,6 +298,13 @@ ds3_status ds3_gemm_workspace_init(void* workspace, size_t workspace_bytes, void
 int ds3_gemm_tail_share_steps(int tail_tiles, int k_steps, int workgroups);
 
 /*
+ * Host logic of the dispatch, exported for its test (no GPU work): which configuration of the kernel for
+ * few rows or few tiles a dense call that names no variant takes on a device of `compute_units`, or -1 where
+ * the main kernel takes it.  (Rows as long as K; longer ones may be left to the main kernel.)
+ */
+int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
+
+/*
  * SwiGLU between the two expert GEMMs (Section 3.3.3, Low-Precision
  * Activation (2) names the operator): h is the BF16 output of the fused
  * gate|up projection, [rows][ldh] with 2*inter valid columns, gate in

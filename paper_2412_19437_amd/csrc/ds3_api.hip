@@ -290,6 +290,14 @@ int ds3_gemm_tail_share_steps(int tail_tiles, int k_steps, int workgroups) {
     return tail_share_steps(tail_tiles, k_steps, workgroups);
 }
 
+int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units) {
+    if (M <= 0 || N <= 0 || K <= 0 || K % 128 || M > kMaxDim || N > kMaxDim || K > kMaxDim || compute_units < 8) return -1;
+    GemmParams p{};
+    p.M = (int)M; p.N = (int)N; p.K = (int)K;
+    p.lda = p.ldb = K;
+    return gemm_skinny_config(p, sb_mode, compute_units);
+}
+
 size_t ds3_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const size_t blk = ds3_gemm_workspace_bytes_v(-1, M, N, K, DS3_BSCALE_128x128);
     const size_t row = ds3_gemm_workspace_bytes_v(-1, M, N, K, DS3_BSCALE_PER_ROW);

@@ -1012,7 +1012,7 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
                        hipStream_t st) {
     if (variant < 0) {
         variant = default_variant(p, mode);
-        if (p.G == 0 && gemm_skinny_preferred(p, num_cus_x8())) {
+        if (p.G == 0 && gemm_skinny_preferred(p, mode, num_cus_x8())) {
             // (this kernel needs no workspace; one that is too small for the shape's tile walk is an error all the same)
             if (ws != nullptr) {
                 size_t need = 0;

@@ -350,16 +350,35 @@ static int skinny_choice(int M, int N, int K, int cus) {
     return best;
 }
 
-// Few rows (nothing is gained from a second row tile: 64x32768x3072 33-38 -> 24 us), or fewer 128x128
-// tiles than compute units.  From there on the main kernel's larger tiles win (us, main / this one:
-// 226 tiles 305x14386x1664 22-29 / 24, 240 tiles 1877x1250x3072 21-23 / 20, 256 tiles 1024x4096x7168
-// 47 / 50, 270 tiles 1152x3712x1536 16 / 20, 384 tiles 2048x3000x1536 16 / 18).
-bool gemm_skinny_preferred(const GemmParams& p, int cus) {
-    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
-    if (p.M > 64 && tiles >= cus) return false;
+// Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 33-38 -> 24 us), or fewer 128x128 tiles than
+// compute units, as far as K lets them.  While every compute unit has at most one of this kernel's 64x128 tiles, a
+// K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two
+// tiles move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a
+// short K shows and a long one does not; the rescale by row costs this kernel more than the main one.  Weights from
+// HBM, us, main kernel / this one, at the worst of the shapes measured beside each line (1600 shapes in four forms, M up
+// to 16384, K 128 .. 18432; within the lines the worst is 1.003 of the main kernel's time, 1.03 on 900 others that the
+// lines were not drawn from; beyond them 1.56):
+//   tiles <= half the compute units   8192x128x18432 by row 103 / 68
+//   tiles <= compute units            385x3392x12288 by row 69 / 68; beyond: 16384x128x18432 by row 111 / 117
+//   more                              1457x2275x4096 34 / 33, by row 4933x444x3072 34 / 34, 552x4096x256 19 / 12;
+//                                     beyond: by row 2560x1444x4096 46 / 47, 9612x210x18432 110 / 173; 589x3746x7168
+//                                     42 / 50; one K-step: 8184x296x128 6.4 / 7.3
+// From as many 128x128 tiles as compute units on the main kernel's two tiles per compute unit win (256 tiles
+// 1024x4096x7168 47 / 50).
+bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus) {
+    if (p.M > 64) {
+        const int64_t tn = (p.N + 127) / 128, tiles = (int64_t)((p.M + 63) / 64) * tn;
+        if ((int64_t)((p.M + 127) / 128) * tn >= cus) return false;
+        const bool rows = mode == DS3_BSCALE_PER_ROW;
+        if (tiles > cus ? p.K < 256 || p.K > (rows ? 3072 : 4096) : 2 * tiles > cus && p.K > 12288) return false;
+    }
     // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel; so do leading dimensions
     // that it refuses (its 128-row tiles reach further than these), for every size alike
     return (int64_t)129 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) && p.N < (1 << 26);
+}
+
+int gemm_skinny_config(const GemmParams& p, ds3_bscale mode, int cus) {
+    return gemm_skinny_preferred(p, mode, cus) ? skinny_choice(p.M, p.N, p.K, cus) : -1;
 }
 
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st) {

@@ -72,8 +72,10 @@ struct GemmParams {
 ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, void* ws, size_t ws_bytes,
                        hipStream_t st);
 // The dense GEMM for few activation rows or few tiles (see ds3_gemm_skinny.hip), and whether launch_gemm
-// takes it for a shape when the caller names no configuration.  cus: compute units of the device.
-bool gemm_skinny_preferred(const GemmParams& p, int cus);
+// takes it for a shape when the caller names no configuration, with which of its own (-1: it does not).
+// cus: compute units of the device.
+bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus);
+int gemm_skinny_config(const GemmParams& p, ds3_bscale mode, int cus);
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
 // The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it.
 bool grouped_skinny_preferred(const GemmParams& p);

@@ -1,0 +1,26 @@
+"""Which kernel a GEMM call takes, by size (host logic, 256 compute units): the lines that were measured, from both
+sides, and that every configuration of the kernel for few rows or few tiles is reached."""
+import pytest
+
+BLOCK, ROW = 0, 1
+
+
+@pytest.mark.parametrize("mode", [BLOCK, ROW])
+@pytest.mark.parametrize("shape,few", [
+    ((1, 1, 128), True), ((64, 32768, 18432), True), ((64, 128, 128), True),            # up to 64 rows: any K
+    ((512, 2048, 18432), True), ((8192, 128, 65536), True),                             # 128 tiles of 64 rows: any K
+    ((513, 2048, 12288), True), ((1024, 2048, 12288), True),                            # up to 256 tiles
+    ((513, 2048, 12416), False), ((1024, 2048, 12416), False), ((4096, 512, 14336), False),
+    ((1025, 2048, 3072), True), ((2048, 1920, 256), True),                              # more: a short K
+    ((1025, 2048, 4224), False), ((384, 7168, 7168), False), ((2048, 1536, 18432), False),
+    ((1025, 2048, 128), False), ((512, 7168, 128), False),                              # ... of two K-steps and more
+    ((2048, 2048, 1024), False), ((65, 32768, 1024), False),                            # 256 tiles of 128 x 128
+])
+def test_dense(ds3, shape, few, mode):
+    assert (ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) >= 0) == few
+
+
+def test_dense_by_row_gives_up_earlier(ds3):
+    f = ds3._L().ds3_gemm_few_tiles_config
+    for k, block, row in ((3072, True, True), (3200, True, False), (4096, True, False), (4224, False, False)):
+        assert (f(2048, 1536, k, BLOCK, 256) >= 0, f(2048, 1536, k, ROW, 256) >= 0) == (block, row), k
