@@ -298,6 +298,16 @@ int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mod
     return gemm_skinny_config(p, sb_mode, compute_units);
 }
 
+int ds3_grouped_gemm_few_rows_tile(int32_t G, int64_t total_rows, int64_t N, int64_t K, int swiglu_quant, int compute_units) {
+    if (G <= 0 || G > 1023 || total_rows <= 0 || N <= 0 || K <= 0 || K % 128 || total_rows > kMaxDim || N > kMaxDim || K > kMaxDim ||
+        compute_units < 8)
+        return 0;
+    GemmParams p{};
+    p.G = G; p.M = (int)total_rows; p.N = (int)N; p.K = (int)K;
+    p.lda = p.ldb = K;
+    return grouped_skinny_rows(p, swiglu_quant != 0, compute_units);
+}
+
 size_t ds3_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const size_t blk = ds3_gemm_workspace_bytes_v(-1, M, N, K, DS3_BSCALE_128x128);
     const size_t row = ds3_gemm_workspace_bytes_v(-1, M, N, K, DS3_BSCALE_PER_ROW);

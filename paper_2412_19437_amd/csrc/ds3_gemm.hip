@@ -1022,9 +1022,10 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
             }
             return launch_gemm_skinny(p, ct, mode, pow2, num_cus_x8(), st);
         }
-        if (p.G > 0 && p.N > 0 && grouped_skinny_preferred(p)) {
+        const int rows = p.G > 0 ? grouped_skinny_rows(p, false, num_cus_x8()) : 0;
+        if (rows > 0) {
             if (ws != nullptr && ws_bytes < kCounterBytes) return DS3_ERR_WORKSPACE;   // (as above)
-            return launch_grouped_skinny(p, ct, false, pow2, st);
+            return launch_grouped_skinny(p, ct, false, rows, pow2, st);
         }
     }
     return pow2 ? launch_variant<true>(p, ct, mode, variant, ws, ws_bytes, nullptr, st)
@@ -1038,9 +1039,10 @@ ds3_status launch_gemm_swiglu_quant(const GemmParams& p, bool pow2, void* ws, si
     // rows and three stages, as the plain grouped GEMM runs by default
     using C = Cfg<256, 128, 4, 2, 3>;
     if (p.G <= 0 || p.N % 256) return DS3_ERR_SHAPE;
-    if (grouped_skinny_preferred(p)) {
+    const int rows = grouped_skinny_rows(p, true, num_cus_x8());
+    if (rows > 0) {
         if (ws != nullptr && ws_bytes < kCounterBytes) return DS3_ERR_WORKSPACE;   // (unused, but checked as ever)
-        return launch_grouped_skinny(p, DS3_BF16, true, pow2, st);
+        return launch_grouped_skinny(p, DS3_BF16, true, rows, pow2, st);
     }
     return pow2 ? launch_one<C, false, true, true, true, true>(p, ws, ws_bytes, nullptr, st)
                 : launch_one<C, false, true, true, false, true>(p, ws, ws_bytes, nullptr, st);

@@ -18,6 +18,8 @@
 // Experts' groups of few rows take the same kernel (`launch_grouped` below).
 // What is left at 32 rows is the ramp and the drain of one round of tiles; the
 // smallest calls are a launch and one latency per stage.
+#include <algorithm>
+
 #include "ds3_dev.h"
 #include "ds3_internal.h"
 
@@ -413,28 +415,44 @@ static ds3_status launch_grouped(GemmParams p, ds3_dtype ct, bool pow2, hipStrea
     return hipGetLastError() == hipSuccess ? DS3_OK : DS3_ERR_LAUNCH;
 }
 
-// Few rows an expert: 32-row tiles up to a mean of 16 rows, 64-row tiles up to 32 (loads spread about their
-// mean; a second row tile of an expert costs more than the padding).  Weights from HBM, gate|up + down, us, main
-// kernel / 32-row / 64-row tiles, H 7168, I 2048: 32 experts of 4 rows 252 / 239 / 240, of 16 rows 256 / 245 / 246,
-// of 32 rows 261 / 278 / 255, of 64 rows 270 / 376 / 302; 8 experts of 4 rows 80 / 72 / 74; H 2048, I 1024, 32
-// experts of 4 rows 51 / 40 / 42, of 32 rows 52 / 53 / 45, of 64 rows 54 / 68 / 58.  Large calls run at the rate
-// the weights come from HBM (6.0 TB/s), small ones were short of bytes in flight.
-static int grouped_rows(const GemmParams& p) {
-    return (int64_t)p.M <= (int64_t)16 * p.G ? 32 : ((int64_t)p.M <= (int64_t)32 * p.G ? 64 : 0);
+// Few rows an expert: 32-row tiles up to a mean of 16 rows, 64-row tiles up to 32, as far as uneven loads cannot make
+// them the slower ones.  The host knows the rows but not whom they belong to.  Where the rows fall on few experts
+// these tiles are up to four times as many as the main kernel's 128-row ones, each with the expert's whole K to walk,
+// and each (expert, row tile) that does not exist is a workgroup that is launched to leave at once (2.3 ns).  So
+// either all tiles that there could be are resident at once, or there are at most four times as many of them and the
+// rows can make at most a quarter (plain: a third, its K is the short one) of a round more of them than there are
+// experts with rows.  Beyond K = 4096 the shorter start of a tile is no longer worth its smaller size, but for gate|up
+// on 32-row tiles, which keep three stages of weights in flight where the main kernel keeps two.
+// Weights from HBM, us, main kernel / this one, gate|up + down.  Within the lines: H 7168, I 2048, 32 experts of 4 rows
+// 158 / 154 + 91 / 81, 8 experts of 4 58 / 54 + 29 / 24; H 2048, I 1024, 32 of 4 31 / 27 + 20 / 15, 8 of 4 20 / 16 + 14 / 8.
+// Over 11299 calls (1 .. 1023 experts, 1 .. 1024 rows) the worst is 1.006 of the main kernel's time where the rows fall
+// evenly, as exp(N(0, 0.3 .. 0.6)), or evenly on a half, an eighth or one of the experts; with exp(N(0, 1 .. 2)) two of
+// 2571 lose (1.20, 1.06), with loads built to need one tile more than a full round of them nine of 2360 (up to 67 / 89).
+// Beyond the lines: gate|up of 32 experts, 512 rows on four of them 63 / 84, 64 experts, 1024 rows on eight 71 / 126,
+// 256 experts, 4096 rows on one 120 / 321; 1023 experts of 16 rows each (H 2048, I 1024) 770 / 1077; plain, 24 experts
+// of 18 rows, N 2048, K 7168 70 / 76.
+static int grouped_rows(const GemmParams& p, bool swiglu_quant, int cus) {
+    if ((int64_t)p.M > (int64_t)32 * p.G) return 0;
+    const int rows = (int64_t)p.M <= (int64_t)16 * p.G ? 32 : 64;
+    if (p.K > 4096 && !(swiglu_quant && rows == 32)) return 0;
+    const int bn = swiglu_quant ? 256 : 128;           // (as launch_grouped_skinny has it)
+    const int64_t cols = ((int64_t)p.N + bn - 1) / bn, slots = (int64_t)cus * (swiglu_quant ? 1 : 2);
+    const int64_t most = std::min<int64_t>((p.M + rows - 1) / rows + p.G, p.M) * cols;      // workgroups launched
+    const int64_t more = (int64_t)((p.M - 1) / rows) * cols;                                 // tiles beyond one an expert
+    if (most > slots && (most > 4 * slots || (swiglu_quant ? 4 : 3) * more > slots)) return 0;
+    return rows;
 }
 
-bool grouped_skinny_preferred(const GemmParams& p) {
-    if (grouped_rows(p) == 0) return false;
-    // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel
-    return (int64_t)257 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) &&
-           ((int64_t)p.M / 32 + p.G + 1) * ((int64_t)p.N / 128 + 1) < (1 << 28);
+int grouped_skinny_rows(const GemmParams& p, bool swiglu_quant, int cus) {
+    // what the kernel's 32-bit offsets do not hold stays with the main kernel
+    return (int64_t)257 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) ? grouped_rows(p, swiglu_quant, cus) : 0;
 }
 
 // Gate|up: 256 weight rows a workgroup, one per compute unit and as many stages as LDS holds; a plain product: 128
 // weight rows, two workgroups per compute unit, so that one's start and end are hidden behind the other (its K is
 // the short one: 256 rows and four stages take 88 us where these take 82).
-ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, bool pow2, hipStream_t st) {
-    if (grouped_rows(p) == 32)
+ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, int rows, bool pow2, hipStream_t st) {
+    if (rows == 32)
         return swiglu_quant ? launch_grouped<SkinnyCfg<4, 2, 4, 1, 4>, true>(p, ct, pow2, st)
                             : launch_grouped<SkinnyCfg<2, 2, 4, 1, 3>, false>(p, ct, pow2, st);
     return swiglu_quant ? launch_grouped<SkinnyCfg<2, 4, 8, 1, 3>, true>(p, ct, pow2, st)

@@ -77,9 +77,10 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
 bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus);
 int gemm_skinny_config(const GemmParams& p, ds3_bscale mode, int cus);
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
-// The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it.
-bool grouped_skinny_preferred(const GemmParams& p);
-ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, bool pow2, hipStream_t st);
+// The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it: the rows of its tiles,
+// or 0 where a call that names no configuration stays with the main kernel.
+int grouped_skinny_rows(const GemmParams& p, bool swiglu_quant, int cus);
+ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, int rows, bool pow2, hipStream_t st);
 // As launch_gemm with the library's own statically allocated workspace (one per device).
 ds3_status launch_gemm_static_scratch(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, hipStream_t st);
 size_t gemm_static_scratch_bytes();

@@ -24,3 +24,17 @@ def test_dense_by_row_gives_up_earlier(ds3):
     f = ds3._L().ds3_gemm_few_tiles_config
     for k, block, row in ((3072, True, True), (3200, True, False), (4096, True, False), (4224, False, False)):
         assert (f(2048, 1536, k, BLOCK, 256) >= 0, f(2048, 1536, k, ROW, 256) >= 0) == (block, row), k
+
+
+@pytest.mark.parametrize("call,tile", [
+    # experts, rows, N, K, SwiGLU epilogue
+    ((32, 128, 4096, 7168, 1), 32), ((32, 128, 7168, 2048, 0), 32), ((8, 32, 7168, 2048, 0), 32),   # decode batches
+    ((32, 512, 1024, 1024, 1), 32), ((32, 513, 1024, 1024, 1), 64), ((32, 1024, 512, 1024, 0), 64), ((32, 1025, 512, 1024, 0), 0),
+    ((32, 512, 4096, 7168, 1), 0), ((64, 1024, 4096, 7168, 1), 0), ((32, 1024, 7168, 2048, 0), 0),  # uneven loads could cost
+    ((256, 4096, 4096, 7168, 1), 0), ((256, 1024, 7168, 2048, 0), 0), ((1023, 1023, 2048, 1024, 0), 0),
+    ((4, 64, 4096, 7168, 1), 32), ((4, 65, 4096, 7168, 1), 0), ((4, 65, 4096, 4096, 1), 64),        # a long K: 32 rows, gate|up
+    ((12, 20, 4096, 14336, 0), 0), ((12, 20, 4096, 4096, 0), 32),
+    ((1023, 16368, 1 << 20, 128, 0), 0), ((1, 1, 1 << 30, 128, 0), 0),                              # more workgroups than a launch holds
+])
+def test_grouped(ds3, call, tile):
+    assert ds3._L().ds3_grouped_gemm_few_rows_tile(*call, 256) == tile
