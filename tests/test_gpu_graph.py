@@ -12,10 +12,13 @@ from tests._gpu_util import announce, dev
 pytestmark = pytest.mark.gpu
 
 
-def test_quantize_and_gemm_in_a_captured_graph(ds3):
-    announce("graph capture")
+# the first leaves a partial round of tiles, which the GEMM shares along K through the workspace: the arrival counters
+# are updated by every replay and left ready for the next; the second runs the kernel for few tiles
+@pytest.mark.parametrize("shape,shared", [((1408, 3072, 1024), True), ((384, 640, 1024), False)])
+def test_quantize_and_gemm_in_a_captured_graph(ds3, shape, shared):
+    announce(f"graph capture {shape}")
     L = ds3._L()
-    M, N, K = 384, 640, 1024
+    M, N, K = shape
     x = dev(wl.cfg2_x(m=M, k=K), bf16=True)
     w = dev(wl.cfg2_w(n=N, k=K), bf16=True)
     qa = torch.empty((M, K), dtype=torch.uint8, device=x.device)
@@ -23,8 +26,7 @@ def test_quantize_and_gemm_in_a_captured_graph(ds3):
     qb = torch.empty((N, K), dtype=torch.uint8, device=x.device)
     sb = torch.empty((N // 128, K // 128), dtype=torch.float32, device=x.device)
     y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    # this shape leaves a partial round of tiles, which the GEMM shares along K through the
-    # workspace: the arrival counters are updated by every replay and left ready for the next
+    assert (L.ds3_gemm_few_tiles_config(M, N, K, ds3.DS3_BSCALE_128x128, 256) < 0) == shared
     ws_bytes = ds3.ds3_gemm_workspace_bytes(M, N, K)
     assert ws_bytes > 0
     ws = ds3.new_gemm_workspace(ws_bytes, x.device)     # prepared once, outside the graph
@@ -62,14 +64,18 @@ def test_quantize_and_gemm_in_a_captured_graph(ds3):
         assert torch.equal(qa, want[0]) and torch.equal(sa, want[1]) and torch.equal(y, want[2]), it
 
 
-def test_expert_ffn_in_a_captured_graph(ds3):
+@pytest.mark.parametrize("tokens,few", [(2048, False), (128, True)])
+def test_expert_ffn_in_a_captured_graph(ds3, tokens, few):
     """quantize -> grouped gate|up GEMM with SwiGLU and the cast in its epilogue -> grouped down GEMM,
     both GEMMs drawing their tiles from the queue in the workspace (one atomic per tile, counters put
-    back by the last workgroup): every replay must equal the eager result bit for bit."""
-    announce("graph capture: expert FFN")
+    back by the last workgroup), or with few rows an expert on the tiles for those: every replay must equal the
+    eager result bit for bit."""
+    announce(f"graph capture: expert FFN, {tokens} tokens")
     L = ds3._L()
-    sizes, off, _ = wl.cfg3_routing(tokens=2048, local=8)
+    sizes, off, _ = wl.cfg3_routing(tokens=tokens, local=8)
     rows, H, I, G = int(off[-1]), 1024, 256, 8
+    for n, k, swiglu in ((2 * I, H, 1), (H, I, 0)):
+        assert (L.ds3_grouped_gemm_few_rows_tile(G, rows, n, k, swiglu, 256) > 0) == few
     x = dev(wl.cfg3_tokens(rows, k=H), bf16=True)
     w13 = dev(wl.interleave_gate_up(wl.cfg3_w13(g=G, inter=I, k=H)), bf16=True)
     w2 = dev(wl.cfg3_w2(g=G, inter=I, k=H), bf16=True)

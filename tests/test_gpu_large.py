@@ -87,7 +87,8 @@ def test_gemm_with_a_4_gb_output(ds3):
 
 def test_gemm_with_a_very_long_inner_dimension(ds3):
     """K = 65536 (512 K-steps): small-integer codes and power-of-two scales keep every partial sum exact,
-    so the FP32 result equals the oracle bit for bit; with and without tail sharing, both scale paths."""
+    so the FP32 result equals the oracle bit for bit; the kernel for few tiles, 128 x 128 tiles with and without tail
+    sharing, both scale paths."""
     m, n, k = 300, 260, 65_536
     announce(f"long K {m}x{n}x{k}")
     rng = np.random.default_rng(9005)
@@ -95,10 +96,11 @@ def test_gemm_with_a_very_long_inner_dimension(ds3):
     a, b = table[rng.integers(0, 6, (m, k))], table[rng.integers(0, 6, (n, k))]
     sa = np.ldexp(1.0, rng.integers(-1, 2, (m, k // 128))).astype(np.float32)
     sb = np.ldexp(1.0, rng.integers(-1, 3, ((n + 127) // 128, k // 128))).astype(np.float32)
+    assert ds3.ds3_gemm_workspace_bytes_v(2, m, n, k) > 0
     ref = orc.gemm_fp8_bs(a, sa, b, sb)
     assert np.array_equal(ref.astype(np.float32).astype(np.float64), ref)
     args = (dev(a), dev(np.ascontiguousarray(sa.T)).t(), dev(b), dev(sb))
     for fn in (ds3.ds3_gemm_fp8_bs, ds3.ds3_gemm_fp8_bs_pow2):
-        for ws in ("auto", None):
-            c = host(fn(*args, out_dtype=torch.float32, workspace=ws))
-            assert np.array_equal(c.astype(np.float64), ref), (fn.__name__, ws)
+        for variant, ws in ((-1, "auto"), (2, "auto"), (2, None)):
+            c = host(fn(*args, out_dtype=torch.float32, variant=variant, workspace=ws))
+            assert np.array_equal(c.astype(np.float64), ref), (fn.__name__, variant, ws)

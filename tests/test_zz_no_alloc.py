@@ -19,8 +19,10 @@ def _rand_codes(rng, shape):
 
 def test_no_alloc_entry_point_matches_the_workspace_entry_point(ds3):
     rng = np.random.default_rng(91)
-    for (m, n, k) in [(2048, 1536, 2048), (384, 640, 1024)]:        # both share tail tiles along K
+    # the first two share tail tiles along K (144 and 264 tiles of 128 x 128), the others run the kernel for few tiles
+    for (m, n, k, shared) in [(2048, 1152, 4224, True), (1333, 3000, 1536, True), (2048, 1536, 2048, False), (384, 640, 1024, False)]:
         announce(f"no-alloc GEMM {m}x{n}x{k}")
+        assert (ds3._L().ds3_gemm_few_tiles_config(m, n, k, ds3.DS3_BSCALE_128x128, 256) < 0) == shared
         assert ds3.ds3_gemm_workspace_bytes(m, n, k) > 0
         a, b = _rand_codes(rng, (m, k)), _rand_codes(rng, (n, k))
         sa = np.exp(rng.standard_normal((m, k // 128))).astype(np.float32)
