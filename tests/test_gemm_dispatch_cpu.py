@@ -2,6 +2,9 @@
 sides, and that every configuration of the kernel for few rows or few tiles is reached."""
 import pytest
 
+from tests import test_gpu_gemm_grouped_few_rows as grouped_tests
+from tests import test_gpu_gemm_skinny as dense_tests
+
 BLOCK, ROW = 0, 1
 
 
@@ -38,3 +41,15 @@ def test_dense_by_row_gives_up_earlier(ds3):
 ])
 def test_grouped(ds3, call, tile):
     assert ds3._L().ds3_grouped_gemm_few_rows_tile(*call, 256) == tile
+
+
+def test_the_gpu_tests_reach_every_configuration(ds3):
+    """The shapes that the kernel's own tests run, which name no variant."""
+    for mode in (BLOCK, ROW):
+        taken = [ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) for shape in dense_tests.SHAPES]
+        assert min(taken) >= 0 and set(taken) == set(range(5)), mode
+    tile = ds3._L().ds3_grouped_gemm_few_rows_tile
+    groups = grouped_tests.GROUPS
+    plain = {tile(len(groups[g]), sum(groups[g]) + 3, n, k, 0, 256) for g, n, k in grouped_tests.PLAIN}
+    swiglu = {tile(len(groups[g]), sum(groups[g]) + 2, 2 * inter, k, 1, 256) for g, inter, k in grouped_tests.SWIGLU}
+    assert plain == swiglu == {32, 64}

@@ -16,7 +16,13 @@ TABLE = np.array([0x00, 0x38, 0x40, 0xB8, 0xC0, 0x80], dtype=np.uint8)   # 0, 1,
 SHAPES = [
     (1, 1, 128), (1, 64, 256), (15, 31, 384), (16, 33, 640), (17, 96, 1152), (31, 32, 128), (32, 130, 2048),
     (33, 129, 896), (63, 4100, 512), (64, 8200, 384), (65, 257, 128), (129, 1000, 1408), (64, 18433, 256),
-    (500, 2049, 384), (1000, 3001, 512), (2049, 65, 768), (1900, 1700, 128),
+    (500, 2049, 384), (1000, 3001, 512), (2049, 65, 768), (1900, 1700, 256),
+    # K split in four: K-step counts of every remainder (23, 24, 33, 26)
+    (17, 130, 2944), (17, 130, 3072), (33, 96, 4224), (9, 130, 3328),
+    # the decode configuration: 128 weight rows, K split in two
+    (32, 18432, 1152), (31, 16500, 640), (1, 16461, 128), (20, 18435, 1024),
+    # 64-row tiles whose ring of stages wraps, K split in two and not at all
+    (200, 3000, 1280), (1000, 3001, 1152),
 ]
 
 
@@ -40,7 +46,8 @@ def test_skinny_exact(ds3, shape, per_row, pow2):
         return buf[:, :k]
 
     fn = ds3.ds3_gemm_fp8_bs_pow2 if pow2 else ds3.ds3_gemm_fp8_bs
-    args = (padded(a, lda), dev(np.ascontiguousarray(sa.T)).t(), padded(b, ldb), dev(sb))
+    sa_kmajor = dev(np.ascontiguousarray(sa.T)).t()
+    args = (padded(a, lda), sa_kmajor, padded(b, ldb), dev(sb))
     mode = ds3.DS3_BSCALE_PER_ROW if per_row else ds3.DS3_BSCALE_128x128
     for accumulate in (False, True):
         cbuf = torch.full((m, ldc), 7.0, dtype=torch.float32, device="cuda:0")
@@ -54,3 +61,31 @@ def test_skinny_exact(ds3, shape, per_row, pow2):
     fn(*args, sb_mode=mode, c=cbuf[:m, :n])
     assert torch.equal(cbuf[:m, :n].cpu(), torch.from_numpy(ref).float().bfloat16())
     assert torch.all(cbuf[:, n:] == 7.0) and torch.all(cbuf[m:] == 7.0), "wrote beyond the output"
+    # row-major activation scales, K-block-major weight scales
+    got = fn(args[0], dev(sa), args[2], dev(np.ascontiguousarray(sb.T)).t(), sb_mode=mode, out_dtype=torch.float32)
+    assert np.array_equal(host(got).astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("pow2", [False, True])
+@pytest.mark.parametrize("per_row", [False, True])
+@pytest.mark.parametrize("shape", [(33, 96, 4224), (33, 129, 896), (31, 16500, 640), (200, 3000, 1280), (1000, 3001, 512)])
+def test_skinny_special_values(ds3, shape, per_row, pow2):
+    """NaN codes, and (FP32 scales) scales of zero, infinity and NaN: what the main kernel makes of them.  Everything
+    else is exact in any order of summation."""
+    m, n, k = shape
+    announce(f"skinny special values {m}x{n}x{k} per_row={per_row} pow2={pow2}")
+    rng = np.random.default_rng(m + n + k)
+    a, b = TABLE[rng.integers(0, 6, (m, k))], TABLE[rng.integers(0, 6, (n, k))]
+    sa = np.ldexp(1.0, rng.integers(-2, 2, (m, k // 128))).astype(np.float32)
+    sb = np.ldexp(1.0, rng.integers(-1, 3, (n if per_row else (n + 127) // 128, k // 128))).astype(np.float32)
+    a[m // 3, k - 1], b[n // 2, 5] = 0x7F, 0xFF
+    if not pow2:
+        for t, vals in ((sa, (0.0, np.inf, np.nan)), (sb, (0.0, -np.inf))):
+            for v in vals:
+                t[rng.integers(0, t.shape[0]), rng.integers(0, t.shape[1])] = v
+    fn = ds3.ds3_gemm_fp8_bs_pow2 if pow2 else ds3.ds3_gemm_fp8_bs
+    args = (dev(a), dev(np.ascontiguousarray(sa.T)).t(), dev(b), dev(sb))
+    kw = dict(sb_mode=ds3.DS3_BSCALE_PER_ROW if per_row else ds3.DS3_BSCALE_128x128)
+    for out in (torch.float32, torch.bfloat16):
+        got, want = host(fn(*args, out_dtype=out, **kw)), host(fn(*args, out_dtype=out, variant=2, workspace=None, **kw))
+        assert np.isnan(want).any() and np.array_equal(got, want, equal_nan=True)
