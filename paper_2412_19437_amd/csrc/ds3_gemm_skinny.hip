@@ -420,14 +420,15 @@ static ds3_status launch_grouped(GemmParams p, ds3_dtype ct, bool pow2, hipStrea
 // these tiles are up to four times as many as the main kernel's 128-row ones, each with the expert's whole K to walk,
 // and each (expert, row tile) that does not exist is a workgroup that is launched to leave at once (2.3 ns).  So
 // either all tiles that there could be are resident at once, or there are at most four times as many of them and the
-// rows can make at most a quarter (plain: a third, its K is the short one) of a round more of them than there are
-// experts with rows.  Beyond K = 4096 the shorter start of a tile is no longer worth its smaller size, but for gate|up
+// rows can make at most a quarter of a round more of them than there are experts with rows (plain, whose K is the
+// short one: half a round, a third with 64-row tiles).  Beyond K = 4096 the shorter start of a tile is no longer worth its smaller size, but for gate|up
 // on 32-row tiles, which keep three stages of weights in flight where the main kernel keeps two.
 // Weights from HBM, us, main kernel / this one, gate|up + down.  Within the lines: H 7168, I 2048, 32 experts of 4 rows
 // 158 / 154 + 91 / 81, 8 experts of 4 58 / 54 + 29 / 24; H 2048, I 1024, 32 of 4 31 / 27 + 20 / 15, 8 of 4 20 / 16 + 14 / 8.
-// Over 11299 calls (1 .. 1023 experts, 1 .. 1024 rows) the worst is 1.006 of the main kernel's time where the rows fall
-// evenly, as exp(N(0, 0.3 .. 0.6)), or evenly on a half, an eighth or one of the experts; with exp(N(0, 1 .. 2)) two of
-// 2571 lose (1.20, 1.06), with loads built to need one tile more than a full round of them nine of 2360 (up to 67 / 89).
+// Over 17679 calls (1 .. 1023 experts, 1 .. 1024 rows): where the rows fall evenly, as exp(N(0, 0.3 .. 0.6)), or evenly on
+// a half, an eighth or one of the experts, one of 9267 takes more than 1.02 of the main kernel's time (1.04, 1023
+// experts); with exp(N(0, 1 .. 2)) six of 3949 (1.20 at most); with loads built to need one tile more than a full round
+// of them 20 of 4463 (67 / 89 at most).
 // Beyond the lines: gate|up of 32 experts, 512 rows on four of them 63 / 84, 64 experts, 1024 rows on eight 71 / 126,
 // 256 experts, 4096 rows on one 120 / 321; 1023 experts of 16 rows each (H 2048, I 1024) 770 / 1077; plain, 24 experts
 // of 18 rows, N 2048, K 7168 70 / 76.
@@ -439,7 +440,7 @@ static int grouped_rows(const GemmParams& p, bool swiglu_quant, int cus) {
     const int64_t cols = ((int64_t)p.N + bn - 1) / bn, slots = (int64_t)cus * (swiglu_quant ? 1 : 2);
     const int64_t most = std::min<int64_t>((p.M + rows - 1) / rows + p.G, p.M) * cols;      // workgroups launched
     const int64_t more = (int64_t)((p.M - 1) / rows) * cols;                                 // tiles beyond one an expert
-    if (most > slots && (most > 4 * slots || (swiglu_quant ? 4 : 3) * more > slots)) return 0;
+    if (most > slots && (most > 4 * slots || (swiglu_quant ? 4 : rows == 32 ? 2 : 3) * more > slots)) return 0;
     return rows;
 }
 
