@@ -5,7 +5,7 @@
 //
 // In Python (ctypes, torch.empty, views, a Stream object) a call took 12-17 us
 // of host time, now 4.8 us, most of it the launch: a small layer's pass of three
-// calls (256x512x1024, FP32 input) goes from 44 to 15 us, its kernels being 10 us.
+// calls (256x512x1024, FP32 input) goes from 45-46 to 16-18 us, its kernels being 12 us.
 #include <Python.h>
 #include <algorithm>
 

@@ -12,12 +12,14 @@
 // does not depend on timing).
 //
 // Measured against the main kernel on MI355X, weights from HBM (us, before -> now;
-// M x N x K): 32x18432x7168 52 -> 31 (2.8 -> 4.3 TB/s of weights), 32x4096x7168
-// 33 -> 12, 256x512x1024 9.4 -> 3.4, 512x2048x2048 12.9 -> 8.0, 1024x1024x4096
-// 19.6 -> 11.6; per-row scales, FP32 output: 512x1024x4096 19.9 -> 9.0.
+// M x N x K): 32x18432x7168 52 -> 33 (2.5 -> 4.0 TB/s of weights), 32x4096x7168
+// 35 -> 13, 256x512x1024 10.2 -> 4.0, 512x2048x2048 15.8 -> 9.1, 1024x1024x4096
+// 27 -> 13.5; per-row scales, accumulating FP32 output: 512x1024x4096 35 -> 15.
 // Experts' groups of few rows take the same kernel (`launch_grouped` below).
-// What is left at 32 rows is the ramp and the drain of one round of tiles; the
-// smallest calls are a launch and one latency per stage.
+// What is left at 32 rows x 18432 is bytes in flight: 144 tiles of 128 weight rows
+// for 256 compute units, two stages of 40 KiB each on their way (tiles of 32 rows
+// fill the chip and take 34 us).  The smallest calls are a launch and one latency
+// per stage.
 #include <algorithm>
 
 #include "ds3_dev.h"
@@ -324,9 +326,11 @@ static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, bool row_scales,
 
 // The configurations and what a call takes with each: `fixed` + one round of tiles after another, a
 // round being K-steps / WK stages of `full` us when every workgroup slot has a tile and `alone` us when
-// few have, plus the sums' way out.  The figures are fits to measured times of 72 shapes (M 1 .. 2048,
-// N 512 .. 24576, K 512 .. 7168, weights from HBM), within 9-14% of each configuration's own; the
-// configuration they pick is on average 4% slower than the best of ten that were tried, 22% at worst.
+// few have, plus the sums' way out.  It ranks the configurations, no more: against measured times of 146
+// shapes that take this kernel (M 1 .. 2048, N 512 .. 18432, K 512 .. 18432, weights from HBM) a
+// configuration's own figure is 8-16% off on average and up to 36% too low where the bytes bind (there is
+// no term for them: 32x18432x7168 21 for 33 us), but the one it picks is 0.7% slower than the best of the
+// five on average, 7% at worst.
 struct SkinnyChoice { int bn, bm, wk, per_cu; float alone, full, out, fixed; };
 constexpr int kSkinnyCfgs = 5;
 constexpr SkinnyChoice kSkinny[kSkinnyCfgs] = {
@@ -352,7 +356,7 @@ static int skinny_choice(int M, int N, int K, int cus) {
     return best;
 }
 
-// Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 33-38 -> 24 us), or fewer 128x128 tiles than
+// Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 37 -> 26 us), or fewer 128x128 tiles than
 // compute units, as far as K lets them.  While every compute unit has at most one of this kernel's 64x128 tiles, a
 // K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two
 // tiles move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a
@@ -365,8 +369,8 @@ static int skinny_choice(int M, int N, int K, int cus) {
 //   more                              1457x2275x4096 34 / 33, by row 4933x444x3072 34 / 34, 552x4096x256 19 / 12;
 //                                     beyond: by row 2560x1444x4096 46 / 47, 9612x210x18432 110 / 173; 589x3746x7168
 //                                     42 / 50; one K-step: 8184x296x128 6.4 / 7.3
-// From as many 128x128 tiles as compute units on the main kernel's two tiles per compute unit win (256 tiles
-// 1024x4096x7168 47 / 50).
+// From as many 128x128 tiles as compute units on calls stay with the main kernel (256 tiles: 1024x4096x7168 47 / 53; a
+// short K would still gain, 2048x2048x1536 21 / 17).
 bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus) {
     if (p.M > 64) {
         const int64_t tn = (p.N + 127) / 128, tiles = (int64_t)((p.M + 63) / 64) * tn;
