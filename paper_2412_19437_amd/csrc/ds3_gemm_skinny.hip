@@ -11,10 +11,11 @@
 // sums meet in LDS in fixed order (no workspace, no second kernel, the result
 // does not depend on timing).
 //
-// Measured against the main kernel on MI355X, weights from HBM (us, before -> now;
-// M x N x K): 32x18432x7168 52 -> 33 (2.5 -> 4.0 TB/s of weights), 32x4096x7168
-// 35 -> 13, 256x512x1024 10.2 -> 4.0, 512x2048x2048 15.8 -> 9.1, 1024x1024x4096
-// 27 -> 13.5; per-row scales, accumulating FP32 output: 512x1024x4096 35 -> 15.
+// Measured against the main kernel on MI355X, kernels alone, weights from HBM
+// (us, before -> now; M x N x K): 32x18432x7168 52 -> 33 (2.5 -> 4.0 TB/s of
+// weights), 32x4096x7168 35 -> 13, 256x512x1024 10.2 -> 4.0, 512x2048x2048 15.8
+// -> 9.1, 1024x1024x4096 27 -> 13.5; per-row scales, accumulating FP32 output:
+// 512x1024x4096 35 -> 15.
 // Experts' groups of few rows take the same kernel (`launch_grouped` below).
 // What is left at 32 rows x 18432 is bytes in flight: 144 tiles of 128 weight rows
 // for 256 compute units, two stages of 40 KiB each on their way (tiles of 32 rows
@@ -358,12 +359,12 @@ static int skinny_choice(int M, int N, int K, int cus) {
 
 // Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 37 -> 26 us), or fewer 128x128 tiles than
 // compute units, as far as K lets them.  While every compute unit has at most one of this kernel's 64x128 tiles, a
-// K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two
-// tiles move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a
-// short K shows and a long one does not; the rescale by row costs this kernel more than the main one.  Weights from
-// HBM, us, main kernel / this one, at the worst of the shapes measured beside each line (1600 shapes in four forms, M up
-// to 16384, K 128 .. 18432; within the lines the worst is 1.003 of the main kernel's time, 1.03 on 900 others that the
-// lines were not drawn from; beyond them 1.56):
+// K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two tiles
+// move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a short K
+// shows and a long one does not; the rescale by row costs this kernel more than the main one.  Weights from HBM,
+// kernels alone, us, main kernel / this one, at the worst of the shapes measured beside each line (1600 shapes in four
+// forms, M up to 16384, K 128 .. 18432; within the lines the worst is 1.003 of the main kernel's time, 1.03 on 900
+// others that the lines were not drawn from; beyond them 1.56):
 //   tiles <= half the compute units   8192x128x18432 by row 103 / 68
 //   tiles <= compute units            385x3392x12288 by row 69 / 68; beyond: 16384x128x18432 by row 111 / 117
 //   more                              1457x2275x4096 34 / 33, by row 4933x444x3072 34 / 34, 552x4096x256 19 / 12;
@@ -420,22 +421,21 @@ static ds3_status launch_grouped(GemmParams p, ds3_dtype ct, bool pow2, hipStrea
 }
 
 // Few rows an expert: 32-row tiles up to a mean of 16 rows, 64-row tiles up to 32, as far as uneven loads cannot make
-// them the slower ones.  The host knows the rows but not whom they belong to.  Where the rows fall on few experts
-// these tiles are up to four times as many as the main kernel's 128-row ones, each with the expert's whole K to walk,
-// and each (expert, row tile) that does not exist is a workgroup that is launched to leave at once (2.3 ns).  So
-// either all tiles that there could be are resident at once, or there are at most four times as many of them and the
-// rows can make at most a quarter of a round more of them than there are experts with rows (plain, whose K is the
-// short one: half a round, a third with 64-row tiles).  Beyond K = 4096 the shorter start of a tile is no longer worth its smaller size, but for gate|up
-// on 32-row tiles, which keep three stages of weights in flight where the main kernel keeps two.
-// Weights from HBM, us, main kernel / this one, gate|up + down.  Within the lines: H 7168, I 2048, 32 experts of 4 rows
-// 158 / 154 + 91 / 81, 8 experts of 4 58 / 54 + 29 / 24; H 2048, I 1024, 32 of 4 31 / 27 + 20 / 15, 8 of 4 20 / 16 + 14 / 8.
-// Over 17679 calls (1 .. 1023 experts, 1 .. 1024 rows): where the rows fall evenly, as exp(N(0, 0.3 .. 0.6)), or evenly on
-// a half, an eighth or one of the experts, one of 9267 takes more than 1.02 of the main kernel's time (1.04, 1023
-// experts); with exp(N(0, 1 .. 2)) six of 3949 (1.20 at most); with loads built to need one tile more than a full round
-// of them 20 of 4463 (67 / 89 at most).
-// Beyond the lines: gate|up of 32 experts, 512 rows on four of them 63 / 84, 64 experts, 1024 rows on eight 71 / 126,
-// 256 experts, 4096 rows on one 120 / 321; 1023 experts of 16 rows each (H 2048, I 1024) 770 / 1077; plain, 24 experts
-// of 18 rows, N 2048, K 7168 70 / 76.
+// them the slower ones.  The host knows the rows but not whom they belong to.  Where the rows fall on few experts these
+// tiles are up to four times as many as the main kernel's 128-row ones, each with the expert's whole K to walk, and
+// each (expert, row tile) that does not exist is a workgroup that is launched to leave at once (2.3 ns).  So either all
+// tiles that there could be are resident at once, or there are at most four times as many of them and the rows can make
+// at most a quarter of a round more of them than there are experts with rows (plain, whose K is the short one: half a
+// round, a third with 64-row tiles).  Beyond K = 4096 the shorter start of a tile is no longer worth its smaller size,
+// but for gate|up on 32-row tiles, which keep three stages of weights in flight where the main kernel keeps two.
+// Weights from HBM, kernels alone, us, main kernel / this one, gate|up + down.  Within the lines: H 7168, I 2048, 32
+// experts of 4 rows 158 / 154 + 91 / 81, 8 experts of 4 58 / 54 + 29 / 24; H 2048, I 1024, 32 of 4 31 / 27 + 20 / 15, 8
+// of 4 20 / 16 + 14 / 8. Over 17679 calls (1 .. 1023 experts, 1 .. 1024 rows): where the rows fall evenly, as exp(N(0,
+// 0.3 .. 0.6)), or evenly on a half, an eighth or one of the experts, one of 9267 takes more than 1.02 of the main
+// kernel's time (1.04, 1023 experts); with exp(N(0, 1 .. 2)) six of 3949 (1.20 at most); with loads built to need one
+// tile more than a full round of them 20 of 4463 (67 / 89 at most). Beyond the lines: gate|up of 32 experts, 512 rows
+// on four of them 63 / 84, 64 experts, 1024 rows on eight 71 / 126, 256 experts, 4096 rows on one 120 / 321; 1023
+// experts of 16 rows each (H 2048, I 1024) 770 / 1077; plain, 24 experts of 18 rows, N 2048, K 7168 70 / 76.
 static int grouped_rows(const GemmParams& p, bool swiglu_quant, int cus) {
     if ((int64_t)p.M > (int64_t)32 * p.G) return 0;
     const int rows = (int64_t)p.M <= (int64_t)16 * p.G ? 32 : 64;
@@ -450,7 +450,8 @@ static int grouped_rows(const GemmParams& p, bool swiglu_quant, int cus) {
 
 int grouped_skinny_rows(const GemmParams& p, bool swiglu_quant, int cus) {
     // what the kernel's 32-bit offsets do not hold stays with the main kernel
-    return (int64_t)257 * p.ldb + p.K < (1ll << 31) && (int64_t)129 * p.lda + p.K < (1ll << 31) ? grouped_rows(p, swiglu_quant, cus) : 0;
+    if ((int64_t)257 * p.ldb + p.K >= (1ll << 31) || (int64_t)129 * p.lda + p.K >= (1ll << 31)) return 0;
+    return grouped_rows(p, swiglu_quant, cus);
 }
 
 // Gate|up: 256 weight rows a workgroup, one per compute unit and as many stages as LDS holds; a plain product: 128
