@@ -19,13 +19,11 @@ __device__ __forceinline__ unsigned int as_u32(float f) { return __builtin_bit_c
 __device__ __forceinline__ float bf16_lo(unsigned int w) { return as_f32(w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned int w) { return as_f32(w & 0xffff0000u); }
 
-// FP32 -> BF16, round to nearest even (finite inputs).
-__device__ __forceinline__ unsigned int f32_to_bf16_rne(float f) {
-    unsigned int u = as_u32(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
+// Two FP32 -> BF16, round to nearest even, the first in the low half: one instruction (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ unsigned int pack_bf16x2(float lo, float hi) {
-    return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
 // Max over the 16 lanes of a DPP row; every lane of the row gets the result.
