@@ -300,9 +300,11 @@ int ds3_gemm_tail_share_steps(int tail_tiles, int k_steps, int workgroups);
 /*
  * Host logic of the dispatch, exported for its test (no GPU work): which configuration of the kernel for
  * few rows or few tiles a dense call that names no variant takes on a device of `compute_units`, or -1 where
- * the main kernel takes it.  (Rows as long as K; longer ones may be left to the main kernel.)
+ * another kernel takes it.  (Rows as long as K; longer ones may be left to the main kernel.)
  */
 int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
+/* ... whether a dense call that names no variant takes the kernel for a short K and a large output (1 or 0), */
+int ds3_gemm_short_k(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
 /* ... and the rows of the tiles that a grouped call of few rows an expert takes, 32 or 64; 0: the main kernel's.
  * swiglu_quant: the call with SwiGLU and the cast in its epilogue (N counts gate and up rows). */
 int ds3_grouped_gemm_few_rows_tile(int32_t G, int64_t total_rows, int64_t N, int64_t K, int swiglu_quant, int compute_units);

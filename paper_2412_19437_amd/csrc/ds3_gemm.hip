@@ -1012,15 +1012,17 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
                        hipStream_t st) {
     if (variant < 0) {
         variant = default_variant(p, mode);
-        if (p.G == 0 && gemm_skinny_preferred(p, mode, num_cus_x8())) {
-            // (this kernel needs no workspace; one that is too small for the shape's tile walk is an error all the same)
+        const bool skinny = p.G == 0 && gemm_skinny_preferred(p, mode, num_cus_x8());
+        if (skinny || (p.G == 0 && gemm_shortk_preferred(p, num_cus_x8()))) {
+            // (these kernels need no workspace; one that is too small for the shape's tile walk is an error all the same)
             if (ws != nullptr) {
                 size_t need = 0;
                 const ds3_status rc = launch_variant<false>(p, ct, mode, variant, nullptr, 0, &need, st);
                 if (rc != DS3_OK) return rc;
                 if (ws_bytes < need) return DS3_ERR_WORKSPACE;
             }
-            return launch_gemm_skinny(p, ct, mode, pow2, num_cus_x8(), st);
+            return skinny ? launch_gemm_skinny(p, ct, mode, pow2, num_cus_x8(), st)
+                          : launch_gemm_shortk(p, ct, mode, pow2, num_cus_x8(), st);
         }
         const int rows = p.G > 0 ? grouped_skinny_rows(p, false, num_cus_x8()) : 0;
         if (rows > 0) {

@@ -77,6 +77,10 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
 bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus);
 int gemm_skinny_config(const GemmParams& p, ds3_bscale mode, int cus);
 ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
+// The dense GEMM for a short K and a large output (see ds3_gemm_shortk.hip), and whether launch_gemm takes it for a
+// call that names no configuration and is not the kernel's above.
+bool gemm_shortk_preferred(const GemmParams& p, int cus);
+ds3_status launch_gemm_shortk(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
 // The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it: the rows of its tiles,
 // or 0 where a call that names no configuration stays with the main kernel.
 int grouped_skinny_rows(const GemmParams& p, bool swiglu_quant, int cus);

@@ -53,3 +53,13 @@ def test_the_gpu_tests_reach_every_configuration(ds3):
     plain = {tile(len(groups[g]), sum(groups[g]) + 3, n, k, 0, 256) for g, n, k in grouped_tests.PLAIN}
     swiglu = {tile(len(groups[g]), sum(groups[g]) + 2, 2 * inter, k, 1, 256) for g, inter, k in grouped_tests.SWIGLU}
     assert plain == swiglu == {32, 64}
+
+
+@pytest.mark.parametrize("mode", [BLOCK, ROW])
+@pytest.mark.parametrize("shape,short", [
+    ((8192, 32768, 512), 1), ((8192, 32768, 640), 0), ((18432, 7168, 128), 1),          # K in registers
+    ((768, 16384, 512), 1), ((767, 16384, 512), 0), ((767, 65536, 256), 1),             # few rows: more than a round of large tiles
+    ((1025, 2048, 512), 0), ((64, 32768, 512), 0), ((1025, 2048, 128), 1),              # the kernel for few rows or tiles comes first
+])
+def test_short_k(ds3, shape, short, mode):
+    assert ds3._L().ds3_gemm_short_k(*shape, mode, 256) == short
