@@ -20,9 +20,11 @@ template <typename V>
 __device__ __forceinline__ void st_stream(uint8_t* p, V v) {
     *reinterpret_cast<V*>(p) = v;
 }
-// Non-temporal store: measured faster only where a kernel reads at least as much as it
-// writes per element and the tensors are large (the fused producers, the optimizer step);
-// the plain quantizers and the transposing kernels are 5-15% slower with it.
+// Non-temporal store: for what is not read again soon (the optimizer step's states and weights,
+// 617 us a step where plain stores of the new weights take 633).  Codes are: the GEMM behind a fused
+// producer finds them in the memory-side cache where they went there by plain stores (8192 x 7168
+// behind RMSNorm, N 576: the GEMM 56 -> 42 us, the producer's time the same; SwiGLU and a 4096 x 7168 x
+// 18432 product 484 -> 477 us).  The plain quantizers and the transposing kernels are 5-15% slower with it.
 template <typename V>
 __device__ __forceinline__ void st_nt(uint8_t* p, V v) {
     __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
@@ -563,7 +565,7 @@ __global__ __launch_bounds__(256) void swiglu_quant_1x128_kernel(
         if (ok[t]) {
             const int64_t col = (kb0 + t) * 128 + lane16 * 8;
             u32x2 c = {cvt4_e4m3(v[0], v[1], v[2], v[3]), cvt4_e4m3(v[4], v[5], v[6], v[7])};
-            st_nt(q + row * ldq + col, c);
+            st_stream(q + row * ldq + col, c);
         }
     }
 }
@@ -652,7 +654,7 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_kernel(
                 widen<Bf16>(w, r);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) r[e] = r[e] * gs.r;
-                if (ok[i]) st_nt(q + row * ldq + col, u32x2{cvt4_e4m3(r[0], r[1], r[2], r[3]), cvt4_e4m3(r[4], r[5], r[6], r[7])});
+                if (ok[i]) st_stream(q + row * ldq + col, u32x2{cvt4_e4m3(r[0], r[1], r[2], r[3]), cvt4_e4m3(r[4], r[5], r[6], r[7])});
             }
         }
 #pragma unroll
