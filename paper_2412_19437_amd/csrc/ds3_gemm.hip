@@ -914,6 +914,21 @@ int tail_share_steps(int tail, int kb, int nslots) {
     return 0;
 }
 
+// Whether cutting a tail tile's `saved` K-steps off a call is worth the exchange of the partial sums (through memory,
+// all of them at the same time: 7 us for a few tiles, twice that where most workgroups hold a piece).  Asked where the
+// caller names no configuration.  `tail` shared tiles an XCD of `cus` compute units, `per_cu` workgroups on each.
+// Kernels alone, us, not shared / shared (K 1024 .. 12288 at 20 tile counts, BF16, FP32, and accumulating by row):
+//   no full round, tail <= half the compute units   128x128: 32 tiles of 128, K 4096 24.7 / 22.2, 3072 16.4 / 19.3;
+//                                                   256x256: 128 tiles, K 4096 48.6 / 44.8, 2048 29.0 / 35.7
+//   no full round, more                             128x128: 256 tiles, K 6144 37.6 / 36.3, 4096 26.6 / 29.6, 1024 9.0 /
+//                                                   19.5; 264 tiles of K 1536 16.8 / 23.5; 304, K 8192 53.0 / 64.5
+//   behind full rounds                              128x128: 576 tiles, K 4096 53.0 / 51.7, 1024 17.5 / 20.1;
+//                                                   256x256: 288 tiles, K 8192 162 / 159, 4096 88.1 / 92.8
+static bool share_pays(int rounds, int tail, int saved, int cus, int per_cu) {
+    const bool few = 2 * tail <= cus;
+    return saved >= (rounds == 0 || per_cu > 1 ? (few ? 16 : 24) : 32);
+}
+
 // Bytes of workspace with which a dense launch of configuration C shares its tail tiles
 // along K (0: the tile count leaves no tail worth sharing).  Mirrors the kernel's rule.
 template <class C>
@@ -933,8 +948,9 @@ static size_t share_bytes(int64_t ntiles, int64_t slots, int kb, int* q_main, in
     return *tail_max ? kCounterBytes + (size_t)8 * *tail_max * 2 * C::BN * C::BM * sizeof(float) : 0;
 }
 
+// `named`: the caller chose the configuration; its tail is shared wherever the workspace allows it.
 template <class C, bool ROWSB, bool OUT_BF16, bool GROUPED, bool POW2, bool SWIQ = false>
-static ds3_status launch_one(GemmParams p, void* ws, size_t ws_bytes, size_t* ws_need, hipStream_t st) {
+static ds3_status launch_one(GemmParams p, bool named, void* ws, size_t ws_bytes, size_t* ws_need, hipStream_t st) {
     if (GROUPED) p.tiles_m = (p.M + C::BM - 1) / C::BM + p.G;
     else p.tiles_m = (p.M + C::BM - 1) / C::BM;
     p.tiles_n = (p.N + C::BN - 1) / C::BN;
@@ -950,8 +966,16 @@ static ds3_status launch_one(GemmParams p, void* ws, size_t ws_bytes, size_t* ws
     // 32-bit byte offsets inside one tile's rows, all below the out-of-range marker
     if ((int64_t)(C::BN + 1) * p.ldb + p.K >= (1ll << 31) || (int64_t)(C::BM + 1) * p.lda + p.K >= (1ll << 31))
         return DS3_ERR_UNSUPPORTED;
-    const bool share = ws != nullptr && need > 0;
+    bool share = ws != nullptr && need > 0;
     if (share && ws_bytes < need) return DS3_ERR_WORKSPACE;
+    if (share && !GROUPED && !named) {
+        const int nslots = (int)(slots / 8), kb = p.K / 128;
+        const int cnt = (int)((ntiles + 7) / 8), cnt_last = (int)(ntiles % cnt);   // tiles of a full chunk, of the one that is not
+        auto keep = [&](int n, int q) { return q > 0 && share_pays(n / nslots, n % nslots, kb - q, nslots / C::WG_PER_CU, C::WG_PER_CU) ? q : 0; };
+        q_main = keep(cnt, q_main);
+        q_last = keep(cnt_last, q_last);
+        share = q_main > 0 || q_last > 0;
+    }
     // Persistent launch: as many workgroups as fit the chip at once (fewer if there
     // are fewer tiles and no tile is shared along K), a multiple of 8 so that every
     // XCD gets the same number.
@@ -973,24 +997,24 @@ static ds3_status launch_one(GemmParams p, void* ws, size_t ws_bytes, size_t* ws
 }
 
 template <class C, bool POW2>
-static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, void* ws, size_t wsb, size_t* need, hipStream_t st) {
+static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool named, void* ws, size_t wsb, size_t* need, hipStream_t st) {
     const bool bf16 = ct == DS3_BF16;
     if (p.G > 0)
-        return bf16 ? launch_one<C, false, true, true, POW2>(p, ws, wsb, need, st) : launch_one<C, false, false, true, POW2>(p, ws, wsb, need, st);
+        return bf16 ? launch_one<C, false, true, true, POW2>(p, named, ws, wsb, need, st) : launch_one<C, false, false, true, POW2>(p, named, ws, wsb, need, st);
     if (mode == DS3_BSCALE_PER_ROW)
-        return bf16 ? launch_one<C, true, true, false, POW2>(p, ws, wsb, need, st) : launch_one<C, true, false, false, POW2>(p, ws, wsb, need, st);
-    return bf16 ? launch_one<C, false, true, false, POW2>(p, ws, wsb, need, st) : launch_one<C, false, false, false, POW2>(p, ws, wsb, need, st);
+        return bf16 ? launch_one<C, true, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, true, false, false, POW2>(p, named, ws, wsb, need, st);
+    return bf16 ? launch_one<C, false, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, false, false, false, POW2>(p, named, ws, wsb, need, st);
 }
 
 int gemm_num_variants() { return 3; }
 
 template <bool POW2>
-static ds3_status launch_variant(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, void* ws, size_t wsb, size_t* need,
-                                 hipStream_t st) {
+static ds3_status launch_variant(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool named, void* ws, size_t wsb,
+                                 size_t* need, hipStream_t st) {
     switch (variant) {
-        case 0: return launch_cfg<Cfg<256, 256, 4, 2, 2>, POW2>(p, ct, mode, ws, wsb, need, st);
-        case 1: return launch_cfg<Cfg<256, 128, 4, 2, 3>, POW2>(p, ct, mode, ws, wsb, need, st);
-        case 2: return launch_cfg<Cfg<128, 128, 2, 2, 2>, POW2>(p, ct, mode, ws, wsb, need, st);
+        case 0: return launch_cfg<Cfg<256, 256, 4, 2, 2>, POW2>(p, ct, mode, named, ws, wsb, need, st);
+        case 1: return launch_cfg<Cfg<256, 128, 4, 2, 3>, POW2>(p, ct, mode, named, ws, wsb, need, st);
+        case 2: return launch_cfg<Cfg<128, 128, 2, 2, 2>, POW2>(p, ct, mode, named, ws, wsb, need, st);
         default: return DS3_ERR_UNSUPPORTED;
     }
 }
@@ -1010,14 +1034,15 @@ static int default_variant(const GemmParams& p, ds3_bscale mode) {
 
 ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, void* ws, size_t ws_bytes,
                        hipStream_t st) {
-    if (variant < 0) {
+    const bool named = variant >= 0;
+    if (!named) {
         variant = default_variant(p, mode);
         const bool skinny = p.G == 0 && gemm_skinny_preferred(p, mode, num_cus_x8());
         if (skinny || (p.G == 0 && gemm_shortk_preferred(p, num_cus_x8()))) {
             // (these kernels need no workspace; one that is too small for the shape's tile walk is an error all the same)
             if (ws != nullptr) {
                 size_t need = 0;
-                const ds3_status rc = launch_variant<false>(p, ct, mode, variant, nullptr, 0, &need, st);
+                const ds3_status rc = launch_variant<false>(p, ct, mode, variant, false, nullptr, 0, &need, st);
                 if (rc != DS3_OK) return rc;
                 if (ws_bytes < need) return DS3_ERR_WORKSPACE;
             }
@@ -1030,8 +1055,8 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
             return launch_grouped_skinny(p, ct, false, rows, pow2, st);
         }
     }
-    return pow2 ? launch_variant<true>(p, ct, mode, variant, ws, ws_bytes, nullptr, st)
-                : launch_variant<false>(p, ct, mode, variant, ws, ws_bytes, nullptr, st);
+    return pow2 ? launch_variant<true>(p, ct, mode, variant, named, ws, ws_bytes, nullptr, st)
+                : launch_variant<false>(p, ct, mode, variant, named, ws, ws_bytes, nullptr, st);
 }
 
 size_t grouped_workspace_bytes() { return kCounterBytes; }
@@ -1046,8 +1071,8 @@ ds3_status launch_gemm_swiglu_quant(const GemmParams& p, bool pow2, void* ws, si
         if (ws != nullptr && ws_bytes < kCounterBytes) return DS3_ERR_WORKSPACE;   // (unused, but checked as ever)
         return launch_grouped_skinny(p, DS3_BF16, true, rows, pow2, st);
     }
-    return pow2 ? launch_one<C, false, true, true, true, true>(p, ws, ws_bytes, nullptr, st)
-                : launch_one<C, false, true, true, false, true>(p, ws, ws_bytes, nullptr, st);
+    return pow2 ? launch_one<C, false, true, true, true, true>(p, true, ws, ws_bytes, nullptr, st)
+                : launch_one<C, false, true, true, false, true>(p, true, ws, ws_bytes, nullptr, st);
 }
 
 __global__ void zero_fill_kernel(uint8_t* c, int64_t row_bytes, int64_t ld_bytes, int64_t rows) {
@@ -1120,7 +1145,7 @@ size_t gemm_workspace_bytes(const GemmParams& p, ds3_bscale mode, int variant) {
     if (variant < 0) variant = default_variant(p, mode);
     size_t need = 0;
     // the requirement depends on the tile configuration only, not on the output type or the scale kind
-    if (launch_variant<false>(p, DS3_BF16, mode, variant, nullptr, 0, &need, nullptr) != DS3_OK) return 0;
+    if (launch_variant<false>(p, DS3_BF16, mode, variant, false, nullptr, 0, &need, nullptr) != DS3_OK) return 0;
     return need;
 }
 

@@ -130,3 +130,26 @@ def test_empty_inner_dimension(ds3):
     assert L.ds3_gemm_fp8_bs(8, 8, 0, None, 0, None, 0, 0, None, 0, None, 0, 0, 0, c.data_ptr(), ds3.DS3_F32, 8, 1, None, 0,
                              torch.cuda.current_stream().cuda_stream) == 0
     assert np.all(host(c) == 3.0)
+
+
+# a call that names no configuration shares tiles only where the K-steps it saves are worth the exchange
+@pytest.mark.parametrize("shape,variant,shared", [
+    ((2048, 2048, 6144), 2, True), ((2048, 2048, 2048), 2, False), ((1333, 3000, 1536), 2, False),
+    ((2000, 9100, 8192), 0, True), ((2000, 9100, 1024), 0, False),
+])
+def test_default_call_shares_where_it_pays(ds3, shape, variant, shared):
+    m, n, k = shape
+    announce(f"default call {shape}, shared {shared}")
+    rng = np.random.default_rng(64)
+    a, b = _rand_codes(rng, (m, k)), _rand_codes(rng, (n, k))
+    sa = np.exp(rng.standard_normal((m, k // 128))).astype(np.float32)
+    sb = np.exp(rng.standard_normal(((n + 127) // 128, k // 128))).astype(np.float32)
+    args = (dev(a), dev(sa), dev(b), dev(sb))
+    assert ds3.ds3_gemm_workspace_bytes(m, n, k) > 0
+    got = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32)
+    whole = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32, variant=variant, workspace=None)
+    pieces = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32, variant=variant)
+    assert not torch.equal(whole, pieces)
+    assert torch.equal(got, pieces if shared else whole)
+    with pytest.raises(ds3.Ds3Error):                # one that is too small for sharing is refused either way
+        ds3.ds3_gemm_fp8_bs(*args, workspace=torch.zeros(16, dtype=torch.uint8, device="cuda:0"))
