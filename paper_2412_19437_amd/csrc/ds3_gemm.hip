@@ -52,16 +52,21 @@ struct Cfg {
     static constexpr int ROWS = BN + BM;
     static constexpr int STAGE = ROWS * 128;           // bytes of codes per K-step
     static constexpr int RPI = NT / 8;                 // tile rows one load instruction of the workgroup covers
-    static constexpr int LPT = ROWS / RPI;             // 16-byte loads per thread per K-step
+    static constexpr int LPT = (ROWS + RPI - 1) / RPI; // 16-byte loads per thread per K-step
+    static constexpr int LAST_WAVES = ROWS % RPI / 8;  // waves that take part in the last of them (0: all)
     // loads of a K-step that are issued right behind the barrier that frees their stage (the
     // rest go out at the head of the next K-step)
     static constexpr int TAILN = LPT < FN ? LPT : FN;
     static constexpr int SCALE_BYTES = 2 * NS * NT * 4;        // [NS][NT] sa + [NS][NT] per-row sb
-    static constexpr int LDS_BYTES = NS * STAGE + SCALE_BYTES + (kMaxGroups + 1) * 4;   // + row-tile prefix of the experts
-    // workgroups that fit one compute unit: 160 KiB of LDS, and two waves per SIMD (the
+    // the epilogue's strips take the last code stage, and what they need beyond it (many narrow waves)
+    static constexpr int EPI_BYTES = WN * WM * 16 * (TN * 4 + 16);
+    static constexpr int CODE_BYTES = NS * STAGE + (EPI_BYTES > STAGE ? EPI_BYTES - STAGE : 0);
+    static constexpr int LDS_BYTES = CODE_BYTES + SCALE_BYTES + (kMaxGroups + 1) * 4;   // + row-tile prefix of the experts
+    // workgroups that fit one compute unit: 160 KiB of LDS, and two or three waves per SIMD (the
     // kernels need more than 128 registers per lane)
-    static constexpr int WG_PER_CU = (160 * 1024 / LDS_BYTES) < (512 / NT) ? (160 * 1024 / LDS_BYTES) : (512 / NT);
-    static_assert(ROWS % RPI == 0 && BN % RPI == 0 && RPI % 16 == 0, "load mapping");
+    static constexpr int WG_PER_CU = NT > 256 || LDS_BYTES > 80 * 1024 ? 1 : 2;
+    static_assert(NT == 256 || NT == 512 || NT == 768, "waves per SIMD");
+    static_assert(ROWS % 8 == 0 && BN % RPI == 0 && RPI % 16 == 0, "load mapping");
     static_assert(BM <= NT && BN <= NT, "scale staging uses one thread per row");
     static_assert(TN <= 128 && 128 % TN == 0, "one weight-scale block per wave");
     static_assert(FM % 2 == 0 && FM >= 2, "activation fragments are double-buffered");
@@ -100,7 +105,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
     constexpr int BN = C::BN, BM = C::BM, NT = C::NT, FN = C::FN, FM = C::FM, STAGE = C::STAGE, NSUB = C::NSUB;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[C::LDS_BYTES];
     constexpr int NS = C::NS;
-    float* const sa_s = reinterpret_cast<float*>(smem + NS * STAGE);           // [NS][NT], first BM used
+    float* const sa_s = reinterpret_cast<float*>(smem + C::CODE_BYTES);         // [NS][NT], first BM used
     float* const sbrow_s = sa_s + NS * NT;                                     // [NS][NT], first BN used (per-row mode)
 
     const int tid = threadIdx.x;
@@ -115,7 +120,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
     // chunks, one per XCD; the workgroups of an XCD take consecutive tiles of
     // their chunk, so the tiles in flight on one L2 form a compact panel.
     int tiles_m = p.tiles_m;
-    int* const gpre = reinterpret_cast<int*>(smem + NS * STAGE + C::SCALE_BYTES);   // [G+1] row tiles before expert g
+    int* const gpre = reinterpret_cast<int*>(smem + C::CODE_BYTES + C::SCALE_BYTES);   // [G+1] row tiles before expert g
     if constexpr (GROUPED) {
         // the host only knows an upper bound on the row tiles; build their prefix over the experts
         if (tid == 0) {
@@ -324,6 +329,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
 
     // i-th 16-byte load of this thread for the K-step at byte offset koff, into LDS stage `stage`
     auto issue_load = [&](const TileCtx& c, int i, int stage, unsigned koff) {
+        if (C::LAST_WAVES != 0 && i == C::LPT - 1 && wave >= C::LAST_WAVES) return;
         const bool is_b = i * C::RPI < BN;
         const int ii = is_b ? i : i - BN / C::RPI;
         // the wave-uniform part of the offset is summed in a scalar register and added last (tied to
@@ -379,7 +385,10 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
     // stages and may stay in flight.
     auto kstep_barrier = [&]() {
         if constexpr (NS == 2) barrier_keep(std::integral_constant<int, 0>{});
-        else if (scale_role != 0) barrier_keep(std::integral_constant<int, C::LPT + 1>{});
+        else if (C::LAST_WAVES != 0 && wave >= C::LAST_WAVES) {
+            if (scale_role != 0) barrier_keep(std::integral_constant<int, C::LPT>{});
+            else barrier_keep(std::integral_constant<int, C::LPT - 1>{});
+        } else if (scale_role != 0) barrier_keep(std::integral_constant<int, C::LPT + 1>{});
         else barrier_keep(std::integral_constant<int, C::LPT>{});
     };
     // the first NS-1 K-steps of the first tile into stages 0 .. NS-2
@@ -698,7 +707,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
         constexpr int CPR = SEG / 16;                      // 16-byte chunks per row segment
         constexpr int PASSES = 16 * CPR / 64;              // 64 lanes move 16 rows x CPR chunks
         static_assert(16 * CPR % 64 == 0, "epilogue mapping");
-        static_assert((NT / 64) * 16 * ROWB <= STAGE, "epilogue strips fit in one code stage");
+        static_assert((NT / 64) * 16 * ROWB <= C::CODE_BYTES - (NS - 1) * STAGE, "epilogue strips");
         // two strips per wave where they fit: the next row group is written while this one's reads return
         constexpr int NSTRIP = (NT / 64) * 16 * ROWB * 2 <= STAGE ? 2 : 1;
         uint8_t* strip0 = smem + (NS - 1) * STAGE + wave * (16 * ROWB * NSTRIP);
@@ -997,13 +1006,19 @@ static ds3_status launch_one(GemmParams p, bool named, void* ws, size_t ws_bytes
 }
 
 template <class C, bool POW2>
+static ds3_status launch_dense(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool named, void* ws, size_t wsb, size_t* need, hipStream_t st) {
+    const bool bf16 = ct == DS3_BF16;
+    if (mode == DS3_BSCALE_PER_ROW)
+        return bf16 ? launch_one<C, true, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, true, false, false, POW2>(p, named, ws, wsb, need, st);
+    return bf16 ? launch_one<C, false, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, false, false, false, POW2>(p, named, ws, wsb, need, st);
+}
+
+template <class C, bool POW2>
 static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool named, void* ws, size_t wsb, size_t* need, hipStream_t st) {
     const bool bf16 = ct == DS3_BF16;
     if (p.G > 0)
         return bf16 ? launch_one<C, false, true, true, POW2>(p, named, ws, wsb, need, st) : launch_one<C, false, false, true, POW2>(p, named, ws, wsb, need, st);
-    if (mode == DS3_BSCALE_PER_ROW)
-        return bf16 ? launch_one<C, true, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, true, false, false, POW2>(p, named, ws, wsb, need, st);
-    return bf16 ? launch_one<C, false, true, false, POW2>(p, named, ws, wsb, need, st) : launch_one<C, false, false, false, POW2>(p, named, ws, wsb, need, st);
+    return launch_dense<C, POW2>(p, ct, mode, named, ws, wsb, need, st);
 }
 
 int gemm_num_variants() { return 3; }
@@ -1032,13 +1047,60 @@ static int default_variant(const GemmParams& p, ds3_bscale mode) {
     return variant;
 }
 
+// Tiles between those sizes, for dense calls that name no configuration and leave the chip unevenly filled: all tiles in
+// ONE round, each a quarter smaller than what the call would run with.  Where 256x256 tiles fill 160 to 256 compute
+// units, 192x256 tiles (12 waves of 64x64; BF16 output and block scales only, other outputs spill) or 256x192 ones that
+// still fit one each take three quarters of the time; where there are more 128x128 tiles than compute units, some hold
+// two of them and the others wait, and 192x128 tiles (12 waves of 64x32, three stages) or, beyond two each, the former
+// are all resident at once.  Up to K = 1152 the two smaller tiles' start and end still hide behind each other.
+// 2800 shapes (200 to 750 tiles of 128x128, K 640 .. 10112), BF16 / FP32 / accumulating by row, time over the former
+// choice's, geometric mean (worst): 256x256 replaced .83 (.96) / .88 (.97) / .83 (.92); more than two 128x128 tiles a
+// compute unit .75 (.92) / .76 (.90) / .88 (1.05); more than one .88 (1.08) / .84 (.98) / .86 (1.01).  us: 8192x576x7168
+// 44.6 -> 40.7, 8192x1536x7168 87 -> 79, 4096x2304x7168 81 -> 65, 1333x3000x7168 54 -> 40, 3000x3000x1536 28 -> 23; by row,
+// accumulating 1536x7168x8192 127 -> 106 (power-of-two scales 99 -> 86).  K <= 1152: 1114x4392x768 1.11 and by row
+// 1792x4827x768 1.34 of the former time.  Power-of-two scales (6900 shapes) make the former tiles faster and not these
+// ones' start and end, so two lines lie further out: 192x128 K 1280 .. 2176 .98 (1.29), from 2304 on .87; 256x192 by row
+// for more than two tiles a compute unit, K 1280 .. 2944 .94 (1.21), from 3072 on .85.
+enum { kTileDefault = -1, kTile256x192 = 0, kTile192x128 = 1, kTile192x256 = 2 };      // (weight rows x activation rows)
+static int between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int64_t cus) {
+    if (p.G > 0) return kTileDefault;
+    // (leading dimensions that any of the tiles refuses stay with the former choice)
+    if ((int64_t)257 * p.ldb + p.K >= (1ll << 31) || (int64_t)257 * p.lda + p.K >= (1ll << 31)) return kTileDefault;
+    auto tiles = [&](int bn, int bm) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+    const bool large = tiles(256, 256) * 8 >= 5 * cus;   // (default_variant's line)
+    const bool rows = mode == DS3_BSCALE_PER_ROW;
+    if (!large && p.K < 1280) return kTileDefault;
+    if (large ? tiles(256, 256) <= cus : tiles(128, 128) > 2 * cus) {
+        if (ct == DS3_BF16 && !rows && tiles(192, 256) <= cus) return kTile192x256;
+        return tiles(256, 192) <= cus && (large || !rows || !pow2 || p.K >= 3072) ? kTile256x192 : kTileDefault;
+    }
+    return !large && tiles(128, 128) > cus && tiles(192, 128) <= cus && (rows || !pow2 || p.K >= 2304) ? kTile192x128 : kTileDefault;
+}
+
+int gemm_between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus) {
+    return gemm_skinny_preferred(p, mode, cus) || gemm_shortk_preferred(p, cus) ? kTileDefault : between_tile(p, ct, mode, pow2, cus);
+}
+
+template <bool POW2>
+static ds3_status launch_between(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int tile, hipStream_t st) {
+    // (one round: no tail to share along K)
+    switch (tile) {
+        case kTile256x192: return launch_dense<Cfg<256, 192, 4, 2, 2>, POW2>(p, ct, mode, false, nullptr, 0, nullptr, st);
+        case kTile192x128: return launch_dense<Cfg<192, 128, 3, 4, 3>, POW2>(p, ct, mode, false, nullptr, 0, nullptr, st);
+        default: return launch_one<Cfg<192, 256, 3, 4, 2>, false, true, false, POW2>(p, false, nullptr, 0, nullptr, st);
+    }
+}
+
 ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int variant, bool pow2, void* ws, size_t ws_bytes,
                        hipStream_t st) {
     const bool named = variant >= 0;
     if (!named) {
         variant = default_variant(p, mode);
-        const bool skinny = p.G == 0 && gemm_skinny_preferred(p, mode, num_cus_x8());
-        if (skinny || (p.G == 0 && gemm_shortk_preferred(p, num_cus_x8()))) {
+        const int cus = num_cus_x8();
+        const bool skinny = p.G == 0 && gemm_skinny_preferred(p, mode, cus);
+        const bool shortk = p.G == 0 && !skinny && gemm_shortk_preferred(p, cus);
+        const int tile = skinny || shortk ? kTileDefault : between_tile(p, ct, mode, pow2, cus);
+        if (skinny || shortk || tile != kTileDefault) {
             // (these kernels need no workspace; one that is too small for the shape's tile walk is an error all the same)
             if (ws != nullptr) {
                 size_t need = 0;
@@ -1046,10 +1108,11 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
                 if (rc != DS3_OK) return rc;
                 if (ws_bytes < need) return DS3_ERR_WORKSPACE;
             }
-            return skinny ? launch_gemm_skinny(p, ct, mode, pow2, num_cus_x8(), st)
-                          : launch_gemm_shortk(p, ct, mode, pow2, num_cus_x8(), st);
+            if (skinny) return launch_gemm_skinny(p, ct, mode, pow2, cus, st);
+            if (shortk) return launch_gemm_shortk(p, ct, mode, pow2, cus, st);
+            return pow2 ? launch_between<true>(p, ct, mode, tile, st) : launch_between<false>(p, ct, mode, tile, st);
         }
-        const int rows = p.G > 0 ? grouped_skinny_rows(p, false, num_cus_x8()) : 0;
+        const int rows = p.G > 0 ? grouped_skinny_rows(p, false, cus) : 0;
         if (rows > 0) {
             if (ws != nullptr && ws_bytes < kCounterBytes) return DS3_ERR_WORKSPACE;   // (as above)
             return launch_grouped_skinny(p, ct, false, rows, pow2, st);

@@ -81,7 +81,10 @@ ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
 // call that names no configuration and is not the kernel's above.
 bool gemm_shortk_preferred(const GemmParams& p, int cus);
 ds3_status launch_gemm_shortk(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st);
-// The same for experts' groups of rows, plain or with SwiGLU and the quantizer behind it: the rows of its tiles,
+// Which of the tiles between the named configurations a dense call takes that names none and is not one of those
+// (see ds3_gemm.hip): 0 .. 2, -1: none of them.
+int gemm_between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus);
+// The kernel for few rows, for experts' groups, plain or with SwiGLU and the quantizer behind it: the rows of its tiles,
 // or 0 where a call that names no configuration stays with the main kernel.
 int grouped_skinny_rows(const GemmParams& p, bool swiglu_quant, int cus);
 ds3_status launch_grouped_skinny(const GemmParams& p, ds3_dtype ct, bool swiglu_quant, int rows, bool pow2, hipStream_t st);

@@ -63,3 +63,24 @@ def test_the_gpu_tests_reach_every_configuration(ds3):
 ])
 def test_short_k(ds3, shape, short, mode):
     assert ds3._L().ds3_gemm_short_k(*shape, mode, 256) == short
+
+
+@pytest.mark.parametrize("shape,c_type,mode,tile", [
+    ((8192, 1536, 7168), 1, 0, 2), ((8192, 1536, 7168), 0, 0, -1), ((8192, 1536, 7168), 1, 1, -1),     # 192 tiles of 256x256: 256 of 192x256, 258 of 256x192
+    ((1536, 7168, 8192), 0, 1, 0), ((1536, 7168, 640), 0, 1, 0), ((1536, 7168, 512), 0, 1, -1),        # 168: 224 of 256x192; the short-K kernel's
+    ((4096, 4096, 7168), 1, 0, -1), ((4096, 18432, 7168), 1, 0, -1),                                   # a full round and more
+    ((8192, 576, 7168), 1, 0, 1), ((8192, 576, 1280), 0, 1, 1), ((8192, 576, 1152), 1, 0, -1),         # 320 of 128x128: 192 of 192x128
+    ((8192, 512, 7168), 1, 0, -1), ((8192, 800, 7168), 1, 0, -1),                                      # one each; no such tile fits
+    ((4096, 2304, 1536), 1, 0, 2), ((4096, 2304, 1536), 0, 0, 0), ((4096, 2304, 1152), 1, 0, -1),      # 576 of 128x128
+    ((64, 32768, 7168), 1, 0, -1), ((0, 576, 7168), 1, 0, -1), ((8192, 576, 7100), 1, 0, -1),
+])
+def test_between_tile(ds3, shape, c_type, mode, tile):
+    assert ds3._L().ds3_gemm_between_tile(*shape, mode, c_type, 0, 256) == tile
+
+
+@pytest.mark.parametrize("shape,c_type,mode,tile", [
+    ((8192, 576, 2304), 1, 0, 1), ((8192, 576, 2176), 1, 0, -1), ((8192, 576, 1280), 0, 1, 1),
+    ((4096, 2304, 3072), 0, 1, 0), ((4096, 2304, 2944), 0, 1, -1), ((4096, 2304, 1280), 1, 0, 2), ((1536, 7168, 640), 0, 1, 0),
+])
+def test_between_tile_with_power_of_two_scales(ds3, shape, c_type, mode, tile):
+    assert ds3._L().ds3_gemm_between_tile(*shape, mode, c_type, 1, 256) == tile
