@@ -12,15 +12,14 @@
 // does not depend on timing).
 //
 // Measured against the main kernel on MI355X, kernels alone, weights from HBM
-// (us, before -> now; M x N x K): 32x18432x7168 52 -> 33 (2.5 -> 4.0 TB/s of
+// (us, before -> now; M x N x K): 32x18432x7168 52 -> 26 (2.5 -> 5.1 TB/s of
 // weights), 32x4096x7168 35 -> 13, 256x512x1024 10.2 -> 4.0, 512x2048x2048 15.8
 // -> 9.1, 1024x1024x4096 27 -> 13.5; per-row scales, accumulating FP32 output:
 // 512x1024x4096 35 -> 15.
 // Experts' groups of few rows take the same kernel (`launch_grouped` below).
-// What is left at 32 rows x 18432 is bytes in flight: 144 tiles of 128 weight rows
-// for 256 compute units, two stages of 40 KiB each on their way (tiles of 32 rows
-// fill the chip and take 34 us).  The smallest calls are a launch and one latency
-// per stage.
+// What is left at 32 rows x 18432 is the compute units without a tile (231 of 256
+// have one) and the start and end of a tile; the smallest calls are a launch and
+// one latency per stage.
 #include <algorithm>
 
 #include "ds3_dev.h"
@@ -38,12 +37,11 @@ struct SkinnyCfg {
     static constexpr int NSA = (BM + 63) / 64;         // activation-scale loads per wave and stage (one row a lane)
     static constexpr int SCALES = (NSA + 1) * 256;     // per wave and stage: the activation scales, then the weight block's
     static constexpr int STAGE = WK * GROUP + WN * WK * SCALES;
-    static constexpr int NB = 2 * FN, NA = BM / (8 * WN);      // code loads per thread and stage: weights, activations
+    static constexpr int NB = 2 * FN, NA = (BM / 8 + WN - 1) / WN;      // code loads per thread and stage: weights, activations
     static constexpr int LOADS = NB + NA + NSA + 1;         // vector-memory operations per wave and stage
     static constexpr int RLD = BN + 4;                 // floats per row of the reduction buffer
     static constexpr int RED = WK * BM * RLD * 4;
     static constexpr int LDS_BYTES = (NS * STAGE > RED ? NS * STAGE : RED);
-    static_assert(BM % (8 * WN) == 0, "load mapping");
     static_assert(FN * 16 <= 64, "one weight-scale block per wave, one weight row a lane");
     static_assert(NS >= 2 && (NS - 2) * LOADS < 64, "vmcnt immediate");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
@@ -134,6 +132,21 @@ __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) 
     const int gchunk = (lane & 7) ^ swz_key(lrow);
     const unsigned voff_b = (unsigned)(lrow * (int)p.ldb + gchunk * 16), voff_a = (unsigned)(lrow * (int)p.lda + gchunk * 16);
     const unsigned step_b = (unsigned)(8 * WN * (int)p.ldb), step_a = (unsigned)(8 * WN * (int)p.lda);
+    // (an odd number of waves: every other load's rows have the other key; where the activation rows are no whole loads of
+    // all waves, the waves beyond the last eight rows move those once more, the same bytes to the same place)
+    [[maybe_unused]] const unsigned voff_b1 = (unsigned)(lrow * (int)p.ldb + (gchunk ^ 1) * 16);
+    constexpr bool kOdd = WN % 2 != 0, kAgain = (BM / 8) % WN != 0;
+    static_assert(!kOdd || kAgain, "load mapping");
+    [[maybe_unused]] int dst_a[C::NA];
+    [[maybe_unused]] unsigned voff_ai[C::NA];
+    if constexpr (kAgain) {
+#pragma unroll
+        for (int i = 0; i < C::NA; ++i) {
+            const int g = min(i * WN + wn, BM / 8 - 1), row = g * 8 + (lane >> 3);
+            dst_a[i] = (BN / 8 + g) * 1024;
+            voff_ai[i] = (unsigned)(row * (int)p.lda + ((lane & 7) ^ swz_key(row)) * 16);
+        }
+    }
     // scales: each wave fetches for itself, an activation row's per lane, and its weight block's or (per-row
     // mode) a weight row's per lane; what lies beyond the last row repeats it
     unsigned soff_a[C::NSA];
@@ -154,8 +167,14 @@ __global__ __launch_bounds__(C::NT) void gemm_skinny_kernel(const GemmParams p) 
 #pragma unroll
         for (int i = 0; i < C::NB + C::NA; ++i) {
             const bool is_b = i < C::NB;
-            const unsigned voff = is_b ? voff_b + (koff + (unsigned)i * step_b) : voff_a + (koff + (unsigned)(i - C::NB) * step_a);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(is_b ? rs_b : rs_a, (lds_ptr_t)(dst + i * (WN * 1024)), 16, (int)voff, 0, 0, 0);
+            unsigned voff;
+            uint8_t* at = dst + i * (WN * 1024);
+            if (is_b) voff = (kOdd && i % 2 ? voff_b1 : voff_b) + (koff + (unsigned)i * step_b);
+            else if constexpr (kAgain) {
+                voff = voff_ai[i - C::NB] + koff;
+                at = codes + stage * C::STAGE + dst_a[i - C::NB];
+            } else voff = voff_a + (koff + (unsigned)(i - C::NB) * step_a);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(is_b ? rs_b : rs_a, (lds_ptr_t)at, 16, (int)voff, 0, 0, 0);
         }
         uint8_t* sd = scales + stage * C::STAGE;
 #pragma unroll
@@ -325,13 +344,12 @@ static ds3_status launch_cfg(const GemmParams& p, ds3_dtype ct, bool row_scales,
     return pow2 ? launch_one<C, false, true>(p, ct, st) : launch_one<C, false, false>(p, ct, st);
 }
 
-// The configurations and what a call takes with each: `fixed` + one round of tiles after another, a
-// round being K-steps / WK stages of `full` us when every workgroup slot has a tile and `alone` us when
-// few have, plus the sums' way out.  It ranks the configurations, no more: against measured times of 146
-// shapes that take this kernel (M 1 .. 2048, N 512 .. 18432, K 512 .. 18432, weights from HBM) a
-// configuration's own figure is 8-16% off on average and up to 36% too low where the bytes bind (there is
-// no term for them: 32x18432x7168 21 for 33 us), but the one it picks is 0.7% slower than the best of the
-// five on average, 7% at worst.
+// The configurations and what a call takes with each: `fixed` + one round of tiles after another, a round being
+// K-steps / WK stages of `full` us when every workgroup slot has a tile and `alone` us when few have, plus the sums' way
+// out.  It ranks the configurations, no more: against measured times of 146 shapes that take this kernel (M 1 .. 2048, N
+// 512 .. 18432, K 512 .. 18432, weights from HBM) a configuration's own figure is 8-16% off on average and more than a
+// third too low where the bytes bind (there is no term for them), but the one it picks is 0.7% slower than the best of
+// the five on average, 7% at worst.  (Sizes that `one_tile_waves` takes aside, below, are not ranked.)
 struct SkinnyChoice { int bn, bm, wk, per_cu; float alone, full, out, fixed; };
 constexpr int kSkinnyCfgs = 5;
 constexpr SkinnyChoice kSkinny[kSkinnyCfgs] = {
@@ -342,7 +360,20 @@ constexpr SkinnyChoice kSkinny[kSkinnyCfgs] = {
     {128, 64, 1, 2, 0.45f, 0.85f, 1.5f, 2.0f},
 };
 
+// Up to 64 rows and 8193 to 24576 weight rows (256 compute units): as many weight rows a tile, in 16s, as give every
+// compute unit at most one of them (48, 64, 80 or 96; the number of waves side by side), and the stages that LDS then
+// holds.  Tiles of 128 rows left up to half of the compute units without work, tiles of 32 some with three where others
+// had two.  Weights from HBM, kernels alone, us, 128- or 32-row tiles / these: 32x18432x7168 31.3 / 26.1, 32x12288x7168
+// 23.4 / 19.0, 1x18432x7168 28.9 / 25.4 (5.2 TB/s), 64x18432x7168 37 / 30; geometric mean over 11800 shapes of K 640 ..
+// 18432, by width: .83 .92 .88 .94 up to 32 rows, .91 .98 .82 .91 up to 64.  128 rows in seven stages instead, 96 KiB
+// in flight: 32x18432x7168 32.1.  Beyond 24576 .97 and with a shorter K a latency per stage is all there is.
+static int one_tile_waves(int M, int N, int K, int cus) {
+    const int w = (N + 16 * cus - 1) / (16 * cus);
+    return M <= 64 && w >= 3 && w <= 6 && K >= 640 ? w : 0;
+}
+
 static int skinny_choice(int M, int N, int K, int cus) {
+    if (one_tile_waves(M, N, K, cus)) return M <= 32 ? 2 : 4;
     int best = 0;
     float best_us = 0.f;
     for (int i = 0; i < kSkinnyCfgs; ++i) {
@@ -393,9 +424,23 @@ ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
     switch (skinny_choice(p.M, p.N, p.K, cus)) {
         case 0: return launch_cfg<SkinnyCfg<1, 2, 2, 4, 4>>(p, ct, rows, pow2, st);
         case 1: return launch_cfg<SkinnyCfg<1, 2, 2, 2, 4>>(p, ct, rows, pow2, st);
-        case 2: return launch_cfg<SkinnyCfg<2, 2, 4, 2, 3>>(p, ct, rows, pow2, st);
+        case 2:
+            switch (one_tile_waves(p.M, p.N, p.K, cus)) {
+                case 3: return launch_cfg<SkinnyCfg<1, 2, 3, 2, 5>>(p, ct, rows, pow2, st);
+                case 4: return launch_cfg<SkinnyCfg<1, 2, 4, 2, 5>>(p, ct, rows, pow2, st);
+                case 5: return launch_cfg<SkinnyCfg<1, 2, 5, 2, 4>>(p, ct, rows, pow2, st);
+                case 6: return launch_cfg<SkinnyCfg<1, 2, 6, 1, 6>>(p, ct, rows, pow2, st);
+                default: return launch_cfg<SkinnyCfg<2, 2, 4, 2, 3>>(p, ct, rows, pow2, st);
+            }
         case 3: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
-        default: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
+        default:
+            switch (one_tile_waves(p.M, p.N, p.K, cus)) {
+                case 3: return launch_cfg<SkinnyCfg<1, 4, 3, 2, 4>>(p, ct, rows, pow2, st);
+                case 4: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
+                case 5: return launch_cfg<SkinnyCfg<1, 4, 5, 2, 3>>(p, ct, rows, pow2, st);
+                case 6: return launch_cfg<SkinnyCfg<1, 4, 6, 1, 5>>(p, ct, rows, pow2, st);
+                default: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
+            }
     }
 }
 

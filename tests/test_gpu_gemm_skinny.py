@@ -89,3 +89,28 @@ def test_skinny_special_values(ds3, shape, per_row, pow2):
     for out in (torch.float32, torch.bfloat16):
         got, want = host(fn(*args, out_dtype=out, **kw)), host(fn(*args, out_dtype=out, variant=2, workspace=None, **kw))
         assert np.isnan(want).any() and np.array_equal(got, want, equal_nan=True)
+
+
+# one tile of 48, 64, 80 or 96 weight rows a compute unit, up to 32 and up to 64 activation rows: odd numbers of waves side by
+# side, activation rows that are no whole loads of all waves, K-steps of both parities and fewer or more than the stages hold
+ONE_TILE = [
+    (32, 8200, 1664), (1, 12288, 640), (17, 12300, 896), (31, 16384, 1024), (32, 16401, 768), (9, 20480, 1408),
+    (32, 20500, 640), (5, 24575, 1152), (33, 8200, 1664), (64, 12285, 640), (40, 13000, 896), (64, 17003, 768), (50, 20480, 1152),
+    (63, 24570, 896),
+]
+
+
+@pytest.mark.parametrize("pow2", [False, True])
+@pytest.mark.parametrize("per_row", [False, True])
+@pytest.mark.parametrize("shape", ONE_TILE)
+def test_one_tile_a_compute_unit(ds3, shape, per_row, pow2):
+    mode = ds3.DS3_BSCALE_PER_ROW if per_row else ds3.DS3_BSCALE_128x128
+    assert ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) == (2 if shape[0] <= 32 else 4)
+    test_skinny_exact(ds3, shape, per_row, pow2)
+
+
+@pytest.mark.parametrize("pow2", [False, True])
+@pytest.mark.parametrize("per_row", [False, True])
+@pytest.mark.parametrize("shape", [(32, 8200, 1664), (9, 20480, 1408), (40, 13000, 896), (64, 17003, 768)])
+def test_one_tile_special_values(ds3, shape, per_row, pow2):
+    test_skinny_special_values(ds3, shape, per_row, pow2)
