@@ -367,9 +367,13 @@ constexpr SkinnyChoice kSkinny[kSkinnyCfgs] = {
 // 23.4 / 19.0, 1x18432x7168 28.9 / 25.4 (5.2 TB/s), 64x18432x7168 37 / 30; geometric mean over 11800 shapes of K 640 ..
 // 18432, by width: .83 .92 .88 .94 up to 32 rows, .91 .98 .82 .91 up to 64.  128 rows in seven stages instead, 96 KiB
 // in flight: 32x18432x7168 32.1.  Beyond 24576 .97 and with a shorter K a latency per stage is all there is.
+// 65 to 128 rows, in one row tile: from 16385 weight rows on (80, 96 or 112 a tile), where the main kernel or 128x64 tiles
+// had more than a round or read the weights twice; 7800 shapes of K 1280 .. 18432 .84 .81 .85 by width (96x18432x7168 55 /
+// 44, 128x24576x1536 18.0 / 15.9); below K = 1280 .98, at 48 or 64 weight rows 1.0 and 1.08.
 static int one_tile_waves(int M, int N, int K, int cus) {
     const int w = (N + 16 * cus - 1) / (16 * cus);
-    return M <= 64 && w >= 3 && w <= 6 && K >= 640 ? w : 0;
+    if (M <= 64) return w >= 3 && w <= 6 && K >= 640 ? w : 0;
+    return M <= 128 && w >= 5 && w <= 7 && K >= 1280 ? w : 0;
 }
 
 static int skinny_choice(int M, int N, int K, int cus) {
@@ -389,8 +393,8 @@ static int skinny_choice(int M, int N, int K, int cus) {
 }
 
 // Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 37 -> 26 us), or fewer 128x128 tiles than
-// compute units, as far as K lets them.  While every compute unit has at most one of this kernel's 64x128 tiles, a
-// K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two tiles
+// compute units, as far as K lets them (and what `one_tile_waves` takes aside).  While every compute unit has at most
+// one of this kernel's 64x128 tiles, a K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two tiles
 // move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a short K
 // shows and a long one does not; the rescale by row costs this kernel more than the main one.  Weights from HBM,
 // kernels alone, us, main kernel / this one, at the worst of the shapes measured beside each line (1600 shapes in four
@@ -408,7 +412,8 @@ bool gemm_skinny_preferred(const GemmParams& p, ds3_bscale mode, int cus) {
         const int64_t tn = (p.N + 127) / 128, tiles = (int64_t)((p.M + 63) / 64) * tn;
         if ((int64_t)((p.M + 127) / 128) * tn >= cus) return false;
         const bool rows = mode == DS3_BSCALE_PER_ROW;
-        if (tiles > cus ? p.K < 256 || p.K > (rows ? 3072 : 4096) : 2 * tiles > cus && p.K > 12288) return false;
+        const bool too_long = tiles > cus ? p.K < 256 || p.K > (rows ? 3072 : 4096) : 2 * tiles > cus && p.K > 12288;
+        if (too_long && one_tile_waves(p.M, p.N, p.K, cus) == 0) return false;
     }
     // what the kernel's 32-bit offsets and its grid do not hold stays with the main kernel; so do leading dimensions
     // that it refuses (its 128-row tiles reach further than these), for every size alike
@@ -434,6 +439,21 @@ ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
             }
         case 3: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
         default:
+            if (p.M > 64) {
+                switch (one_tile_waves(p.M, p.N, p.K, cus)) {
+                    case 5: return launch_cfg<SkinnyCfg<1, 8, 5, 1, 5>>(p, ct, rows, pow2, st);
+                    case 6: return launch_cfg<SkinnyCfg<1, 8, 6, 1, 4>>(p, ct, rows, pow2, st);
+                    case 7: return launch_cfg<SkinnyCfg<1, 8, 7, 1, 4>>(p, ct, rows, pow2, st);
+                    default: break;
+                }
+                // One 128x64 tile a compute unit at most: there is room for a second group of waves, and twice the bytes in
+                // flight.  4000 shapes of 129 to 256 tiles, time over that of one group: K 1024 .. 10112 .89, by row .87
+                // (1.02 at worst; 768x1536x7168 30.8 / 24.6 us, 1024x2048x7168 31.7 / 29.4, by row 768x1536x8192 38 / 30);
+                // below .93 (1.08).  One group and six stages instead 1.03.
+                if (p.K >= 1024 && (int64_t)((p.M + 63) / 64) * ((p.N + 127) / 128) <= cus)
+                    return launch_cfg<SkinnyCfg<2, 4, 4, 2, 3>>(p, ct, rows, pow2, st);
+                return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
+            }
             switch (one_tile_waves(p.M, p.N, p.K, cus)) {
                 case 3: return launch_cfg<SkinnyCfg<1, 4, 3, 2, 4>>(p, ct, rows, pow2, st);
                 case 4: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);

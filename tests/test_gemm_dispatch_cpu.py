@@ -84,3 +84,12 @@ def test_between_tile(ds3, shape, c_type, mode, tile):
 ])
 def test_between_tile_with_power_of_two_scales(ds3, shape, c_type, mode, tile):
     assert ds3._L().ds3_gemm_between_tile(*shape, mode, c_type, 1, 256) == tile
+
+
+@pytest.mark.parametrize("mode", [BLOCK, ROW])
+@pytest.mark.parametrize("shape,few", [
+    ((128, 16385, 7168), True), ((128, 28672, 7168), True), ((65, 18432, 1280), True),          # one tile a compute unit
+    ((128, 16385, 18432), True), ((128, 16384, 18432), False), ((128, 28673, 7168), False), ((129, 18432, 7168), False),
+])
+def test_dense_one_tile_a_compute_unit(ds3, shape, few, mode):
+    assert (ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) >= 0) == few

@@ -97,6 +97,8 @@ ONE_TILE = [
     (32, 8200, 1664), (1, 12288, 640), (17, 12300, 896), (31, 16384, 1024), (32, 16401, 768), (9, 20480, 1408),
     (32, 20500, 640), (5, 24575, 1152), (33, 8200, 1664), (64, 12285, 640), (40, 13000, 896), (64, 17003, 768), (50, 20480, 1152),
     (63, 24570, 896),
+    (65, 16400, 1280), (128, 20480, 1664), (97, 20481, 1408), (128, 24570, 1280), (80, 24577, 1792), (127, 28672, 1280),
+    (1000, 1500, 1152), (130, 9000, 1024), (513, 3999, 1280),      # 128x64 tiles, two groups of waves
 ]
 
 
@@ -111,6 +113,7 @@ def test_one_tile_a_compute_unit(ds3, shape, per_row, pow2):
 
 @pytest.mark.parametrize("pow2", [False, True])
 @pytest.mark.parametrize("per_row", [False, True])
-@pytest.mark.parametrize("shape", [(32, 8200, 1664), (9, 20480, 1408), (40, 13000, 896), (64, 17003, 768)])
+@pytest.mark.parametrize("shape", [(32, 8200, 1664), (9, 20480, 1408), (40, 13000, 896), (64, 17003, 768), (97, 20481, 1408),
+                                   (1000, 1500, 1152)])
 def test_one_tile_special_values(ds3, shape, per_row, pow2):
     test_skinny_special_values(ds3, shape, per_row, pow2)
