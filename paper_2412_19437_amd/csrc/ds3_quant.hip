@@ -572,13 +572,35 @@ __global__ __launch_bounds__(256) void swiglu_quant_1x128_kernel(
 
 // =============================================================================
 // RMSNorm fused with the 1x128 quantizer of the following Linear's input: one
-// workgroup per row.  The row (at most 8192 BF16 elements) stays in registers
+// workgroup per row (narrow rows: one wave, below).  The row (at most 8192 BF16 elements) stays in registers
 // between the sum of squares and the cast; each of the 16 DPP rows of the
 // workgroup then handles every sixteenth 1x128 tile exactly as the stand-alone
 // quantizer does.  The normalised activation is rounded to BF16 first (it is a
 // BF16 tensor for every other consumer) and optionally written out.
 // =============================================================================
 constexpr int kNormMaxGranules = 4;               // 16-byte granules per lane: rows of up to 4 * 2048 elements
+
+// One granule (eight elements of a lane) of a row from its sum of squares on: normalised, rounded to BF16, cast.
+__device__ __forceinline__ void norm_quant_granule(u32x4 g, f32x4 g0, f32x4 g1, float rstd, bool ok, int64_t row, int64_t kb, int lane16,
+                                                   uint8_t* y, int64_t ldy_bytes, uint8_t* q, int64_t ldq, float* s, int64_t ssr,
+                                                   int64_t ssk, int pow2) {
+    const int64_t col = (kb << 7) + lane16 * 8;
+    float v[8];
+    widen<Bf16>(g, v);
+    const float gmv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = v[e] * rstd * gmv[e];
+    const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+    if (y != nullptr && ok) st_nt(y + row * ldy_bytes + col * 2, w);
+    const unsigned int m = row16_max_bits(granule_amax_bits<Bf16>(w));
+    const GroupScale gs = group_scale(as_f32(m), pow2);
+    if (lane16 == 0) s[row * ssr + kb * ssk] = gs.s;
+    float r[8];
+    widen<Bf16>(w, r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = r[e] * gs.r;
+    if (ok) st_stream(q + row * ldq + col, u32x2{cvt4_e4m3(r[0], r[1], r[2], r[3]), cvt4_e4m3(r[4], r[5], r[6], r[7])});
+}
 
 __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_kernel(
     const uint8_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx_bytes, const float* __restrict__ gamma,
@@ -638,27 +660,73 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_kernel(
 #pragma unroll
         for (int i = 0; i < kNormMaxGranules; ++i) {
             const int64_t kb = 16 * i + t16;
-            const int64_t col = (kb << 7) + lane16 * 8;
-            if ((kb << 7) < cols) {               // a whole DPP row decides together
-                float v[8];
-                widen<Bf16>(g[i], v);
-                const float gmv[8] = {gm[i][0].x, gm[i][0].y, gm[i][0].z, gm[i][0].w, gm[i][1].x, gm[i][1].y, gm[i][1].z, gm[i][1].w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] * rstd * gmv[e];
-                const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-                if (y != nullptr && ok[i]) st_nt(y + row * ldy_bytes + col * 2, w);
-                const unsigned int m = row16_max_bits(granule_amax_bits<Bf16>(w));
-                const GroupScale gs = group_scale(as_f32(m), pow2);
-                if (lane16 == 0) s[row * ssr + kb * ssk] = gs.s;
-                float r[8];
-                widen<Bf16>(w, r);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) r[e] = r[e] * gs.r;
-                if (ok[i]) st_stream(q + row * ldq + col, u32x2{cvt4_e4m3(r[0], r[1], r[2], r[3]), cvt4_e4m3(r[4], r[5], r[6], r[7])});
-            }
+            if ((kb << 7) < cols)                 // a whole DPP row decides together
+                norm_quant_granule(g[i], gm[i][0], gm[i][1], rstd, ok[i], row, kb, lane16, y, ldy_bytes, q, ldq, s, ssr, ssk, pow2);
         }
 #pragma unroll
         for (int i = 0; i < kNormMaxGranules; ++i) g[i] = gn[i];
+    }
+}
+
+// Rows of up to 2048 elements: one WAVE per row.  A workgroup per row has at most a quarter of the granules a lane could
+// hold, and the row's chain (load, sum, barrier, root, scale, cast) bounds it.  Here granule i of a lane is what wave i of
+// that workgroup would hold, and the granules' sums are kept apart until they meet in the same order, so the result is
+// the same bit for bit; there is no barrier.  8192 rows, us, workgroup / wave: 512 15.5 / 6.5 (the launch and one
+// latency), 1024 17.6 / 8.4, 1536 19.5 / 11.6, 2048 21.4 / 14.2 (3.5 TB/s); with eight granules 3072 25.4 / 26.2, 4096 30.0 /
+// 32.5, so wider rows stay with the workgroup.
+template <int G>
+__global__ __launch_bounds__(256) void rmsnorm_quant_1x128_narrow_kernel(
+    const uint8_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx_bytes, const float* __restrict__ gamma,
+    float eps, uint8_t* __restrict__ y, int64_t ldy_bytes, uint8_t* __restrict__ q, int64_t ldq,
+    float* __restrict__ s, int64_t ssr, int64_t ssk, int pow2) {
+    const int lane16 = threadIdx.x & 15, t4 = (threadIdx.x >> 4) & 3;
+    f32x4 gm[G][2];
+    bool ok[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int64_t col = ((int64_t)(4 * i + t4) << 7) + lane16 * 8;
+        ok[i] = col < cols;
+        gm[i][0] = gm[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (ok[i]) {
+            gm[i][0] = *reinterpret_cast<const f32x4*>(gamma + col);
+            gm[i][1] = *reinterpret_cast<const f32x4*>(gamma + col + 4);
+        }
+    }
+    for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += (int64_t)gridDim.x * 4) {
+        u32x4 g[G];
+        float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int64_t col = ((int64_t)(4 * i + t4) << 7) + lane16 * 8;
+            g[i] = u32x4{0u, 0u, 0u, 0u};
+            if (ok[i]) g[i] = ld_stream(x + row * ldx_bytes + col * 2);
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            float v[8];
+            widen<Bf16>(g[i], v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) part[i] = __builtin_fmaf(v[e], v[e], part[i]);
+        }
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            float ss = part[w];
+            ss += as_f32(dpp_u32<0xB1>(as_u32(ss)));
+            ss += as_f32(dpp_u32<0x4E>(as_u32(ss)));
+            ss += as_f32(dpp_u32<0x141>(as_u32(ss)));
+            ss += as_f32(dpp_u32<0x140>(as_u32(ss)));
+            ss += __shfl_xor(ss, 16);
+            ss += __shfl_xor(ss, 32);
+            part[w] = ss;
+        }
+        const float ss = (part[0] + part[1]) + (part[2] + part[3]);
+        const float rstd = 1.0f / sqrtf(ss / (float)cols + eps);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int64_t kb = 4 * i + t4;
+            if ((kb << 7) < cols)
+                norm_quant_granule(g[i], gm[i][0], gm[i][1], rstd, ok[i], row, kb, lane16, y, ldy_bytes, q, ldq, s, ssr, ssk, pow2);
+        }
     }
 }
 
@@ -890,6 +958,16 @@ ds3_status launch_rmsnorm_quant_1x128(const void* x, int64_t rows, int64_t cols,
     if (cols > (int64_t)kNormMaxGranules * 2048) return DS3_ERR_UNSUPPORTED;
     // four workgroups per compute unit (all resident at once), each walking rows a grid apart
     const int64_t grid = rows < 1024 ? rows : 1024;
+    if (cols <= 2048) {
+        const dim3 narrow((unsigned)(rows < 8192 ? (rows + 3) / 4 : 2048));      // eight workgroups per compute unit
+        auto run = [&](auto kernel) {
+            kernel<<<narrow, 256, 0, st>>>((const uint8_t*)x, rows, cols, ldx * 2, gamma, eps, (uint8_t*)y, ldy * 2, q, ldq, s, ssr, ssk, pow2);
+        };
+        if (cols <= 512) run(rmsnorm_quant_1x128_narrow_kernel<1>);
+        else if (cols <= 1024) run(rmsnorm_quant_1x128_narrow_kernel<2>);
+        else run(rmsnorm_quant_1x128_narrow_kernel<4>);
+        return launch_status();
+    }
     rmsnorm_quant_1x128_kernel<<<dim3((unsigned)grid), 256, 0, st>>>(
         (const uint8_t*)x, rows, cols, ldx * 2, gamma, eps, (uint8_t*)y, ldy * 2, q, ldq, s, ssr, ssk, pow2);
     return launch_status();

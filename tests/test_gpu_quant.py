@@ -248,3 +248,10 @@ def test_e5m6_device_rounding_on_every_code_and_tie(ds3):
     q_ref, s_ref = orc.quant_act_1x128_e5m6(x)
     assert np.all(s_ref == 1.0)
     _cmp_codes_scales(q, s, q_ref, s_ref, "e5m6 sweep")
+
+
+@pytest.mark.parametrize("pow2", [False, True])
+@pytest.mark.parametrize("shape", [(1, 8), (5, 128), (3, 504), (6, 512), (7, 520), (4, 1024), (5, 1032), (4, 2048), (3, 2056), (8197, 264)])
+def test_rmsnorm_of_narrow_rows(ds3, shape, pow2):
+    """A wave per row up to 2048 columns: every number of granules, partly filled ones, more rows than the grid holds."""
+    test_rmsnorm_fused_with_quantizer(ds3, shape, pow2)
