@@ -711,7 +711,18 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
         // two strips per wave where they fit: the next row group is written while this one's reads return
         constexpr int NSTRIP = (NT / 64) * 16 * ROWB * 2 <= STAGE ? 2 : 1;
         uint8_t* strip0 = smem + (NS - 1) * STAGE + wave * (16 * ROWB * NSTRIP);
-        uint8_t* c_base = reinterpret_cast<uint8_t*>(p.c);
+        // The output's address and leading dimension in registers of their own where the compiler, short of scalar
+        // registers, otherwise spills them with the kernel arguments that were loaded beside them and fetches the whole
+        // group back in front of every store: 1815 lane reads in the 256x256 kernel (284 with this), 1413 (237) with 192
+        // activation rows, 661 (281) in the 192x128 ones.  256x256, BF16 output and block scales, time over that of the
+        // conversion by integer operations, whose registers happened to suffice: 1.045 without, .979 with (3500 shapes;
+        // 8192x24576x1536 332 -> 326 us, 8192x7168x1536 99.6 -> 96.4); 192x128 .986 of the time without.  The other kernels
+        // read few lanes as it is and lose up to 1.5%.
+        constexpr bool kOwnArgs = OUT_BF16 && !ROWSB && !GROUPED && ((BN == 256 && BM >= 192 && !POW2) || (BN == 192 && BM == 128));
+        uint64_t c_bits = reinterpret_cast<uint64_t>(p.c);
+        int64_t ldc = p.ldc;
+        if constexpr (kOwnArgs) asm volatile("" : "+s"(c_bits), "+s"(ldc));
+        uint8_t* c_base = (uint8_t*)(__attribute__((address_space(1))) uint8_t*)c_bits;   // (global, not flat, accesses)
         const int n_w0 = wn * C::TN;                       // first column of this wave inside the tile
         // Accumulating FP32 output: the old values of fragment row group j+1 are fetched
         // while group j is transposed and stored, so the read-modify-write does not
@@ -725,7 +736,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
                 const int nl = n_w0 + (idx % CPR) * (16 / ESZ);
                 dstv[ps] = f32x4{0.f, 0.f, 0.f, 0.f};
                 if (ml < cur.m_rows && nl + 16 / ESZ <= cur.n_rows)
-                    dstv[ps] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(c_base + ((int64_t)(cur.m0 + ml) * p.ldc + cur.n0 + nl) * ESZ));
+                    dstv[ps] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(c_base + ((int64_t)(cur.m0 + ml) * ldc + cur.n0 + nl) * ESZ));
             }
         };
         const bool accum = !OUT_BF16 && p.accumulate;
@@ -771,7 +782,7 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
                 const int nl = n_w0 + ch * (16 / ESZ);     // first column of this chunk inside the tile
                 const u32x4 w = wv[ps];
                 if (ml >= cur.m_rows || nl >= cur.n_rows) continue;
-                uint8_t* gp = c_base + ((int64_t)(cur.m0 + ml) * p.ldc + cur.n0 + nl) * ESZ;
+                uint8_t* gp = c_base + ((int64_t)(cur.m0 + ml) * ldc + cur.n0 + nl) * ESZ;
                 if (nl + 16 / ESZ <= cur.n_rows) {
                     if constexpr (OUT_BF16) {
                         __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gp));
