@@ -308,6 +308,9 @@ int ds3_gemm_short_k(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int co
 /* ... which tile it takes between the variants' sizes (0: 256 weight rows x 192, 1: 192 x 128, 2: 192 x 256; -1: none), */
 int ds3_gemm_between_tile(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int pow2,
                           int compute_units);
+/* ... whether it shares tiles along K where it is given a workspace (1 or 0), */
+int ds3_gemm_tail_shared(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int accumulate, int pow2,
+                         int compute_units);
 /* ... and the rows of the tiles that a grouped call of few rows an expert takes, 32 or 64; 0: the main kernel's.
  * swiglu_quant: the call with SwiGLU and the cast in its epilogue (N counts gate and up rows). */
 int ds3_grouped_gemm_few_rows_tile(int32_t G, int64_t total_rows, int64_t N, int64_t K, int swiglu_quant, int compute_units);

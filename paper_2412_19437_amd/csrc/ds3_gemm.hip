@@ -934,19 +934,19 @@ int tail_share_steps(int tail, int kb, int nslots) {
     return 0;
 }
 
-// Whether cutting a tail tile's `saved` K-steps off a call is worth the exchange of the partial sums (through memory,
-// all of them at the same time: 7 us for a few tiles, twice that where most workgroups hold a piece).  Asked where the
-// caller names no configuration.  `tail` shared tiles an XCD of `cus` compute units, `per_cu` workgroups on each.
-// Kernels alone, us, not shared / shared (K 1024 .. 12288 at 20 tile counts, BF16, FP32, and accumulating by row):
-//   no full round, tail <= half the compute units   128x128: 32 tiles of 128, K 4096 24.7 / 22.2, 3072 16.4 / 19.3;
-//                                                   256x256: 128 tiles, K 4096 48.6 / 44.8, 2048 29.0 / 35.7
-//   no full round, more                             128x128: 256 tiles, K 6144 37.6 / 36.3, 4096 26.6 / 29.6, 1024 9.0 /
-//                                                   19.5; 264 tiles of K 1536 16.8 / 23.5; 304, K 8192 53.0 / 64.5
-//   behind full rounds                              128x128: 576 tiles, K 4096 53.0 / 51.7, 1024 17.5 / 20.1;
-//                                                   256x256: 288 tiles, K 8192 162 / 159, 4096 88.1 / 92.8
+// Whether cutting a tail tile's `saved` K-steps off a call is worth the exchange of the partial sums (through memory, all
+// of them at the same time).  Asked where the caller names no configuration.  `tail` shared tiles an XCD of `cus` compute
+// units, `per_cu` workgroups on each.
+//   Behind full rounds the exchange costs about 8 K-steps of 256x256 tiles, 6 of 128x128 ones.
+//   Without one, a tail of up to one tile a compute unit leaves half of the workgroup slots idle, and sharing also puts
+//   these to work; the more tiles there are to exchange, the dearer.  Beyond one tile a unit there is less to gain.
+// 15600 calls, operands from HBM and from the caches, every output form, time over that of sharing always (in brackets:
+// the worst, and what is above 1.03): 256x256 behind rounds .968 (1.10, 1%), 128x128 behind rounds .911 (1.05, 1%), no
+// round and up to one a unit .975 (1.15, 1.5%: a long K with all operands from HBM), more .844 (1.17, 1.3%); the better
+// of the two each time .966, .909, .960, .837; 16 to 32 K-steps as the line .986 (1.19, 25%), .912, .978 (1.38, 19%), .843.
 static bool share_pays(int rounds, int tail, int saved, int cus, int per_cu) {
-    const bool few = 2 * tail <= cus;
-    return saved >= (rounds == 0 || per_cu > 1 ? (few ? 16 : 24) : 32);
+    if (rounds > 0) return saved >= (per_cu > 1 ? 6 : 8);
+    return tail > cus ? saved >= 14 : saved >= 2 && 2 * saved >= tail - 12;
 }
 
 // Bytes of workspace with which a dense launch of configuration C shares its tail tiles
@@ -966,6 +966,13 @@ static size_t share_bytes(int64_t ntiles, int64_t slots, int kb, int* q_main, in
     }
     // arrival counters, then two partial tiles for every tile that may be shared
     return *tail_max ? kCounterBytes + (size_t)8 * *tail_max * 2 * C::BN * C::BM * sizeof(float) : 0;
+}
+
+// Whether a call that names no configuration shares its tail; asked of the full chunks, which end last.
+template <class C>
+static bool share_default(int64_t ntiles, int64_t slots, int kb, int q_main) {
+    const int nslots = (int)(slots / 8), cnt = (int)((ntiles + 7) / 8);
+    return q_main > 0 && share_pays(cnt / nslots, cnt % nslots, kb - q_main, nslots / C::WG_PER_CU, C::WG_PER_CU);
 }
 
 // `named`: the caller chose the configuration; its tail is shared wherever the workspace allows it.
@@ -988,14 +995,7 @@ static ds3_status launch_one(GemmParams p, bool named, void* ws, size_t ws_bytes
         return DS3_ERR_UNSUPPORTED;
     bool share = ws != nullptr && need > 0;
     if (share && ws_bytes < need) return DS3_ERR_WORKSPACE;
-    if (share && !GROUPED && !named) {
-        const int nslots = (int)(slots / 8), kb = p.K / 128;
-        const int cnt = (int)((ntiles + 7) / 8), cnt_last = (int)(ntiles % cnt);   // tiles of a full chunk, of the one that is not
-        auto keep = [&](int n, int q) { return q > 0 && share_pays(n / nslots, n % nslots, kb - q, nslots / C::WG_PER_CU, C::WG_PER_CU) ? q : 0; };
-        q_main = keep(cnt, q_main);
-        q_last = keep(cnt_last, q_last);
-        share = q_main > 0 || q_last > 0;
-    }
+    if (share && !GROUPED && !named) share = share_default<C>(ntiles, slots, p.K / 128, q_main);
     // Persistent launch: as many workgroups as fit the chip at once (fewer if there
     // are fewer tiles and no tile is shared along K), a multiple of 8 so that every
     // XCD gets the same number.
@@ -1046,15 +1046,14 @@ static ds3_status launch_variant(const GemmParams& p, ds3_dtype ct, ds3_bscale m
 }
 
 // The tile configuration a shape runs with when the caller does not name one.
-static int default_variant(const GemmParams& p, ds3_bscale mode) {
+static int default_variant(const GemmParams& p, int cus) {
     // the 256x256 tile; the ragged expert groups take 256x128 tiles in three stages (their
     // weights come from HBM, not from the L2, and want the deeper prefetch; 128-row tiles
     // also pad less); problems with too few large tiles to fill the chip take 128x128 tiles,
     // two workgroups per CU
-    (void)mode;
     int variant = p.G > 0 ? 1 : 0;
     const int64_t big = (int64_t)((p.M + 255) / 256) * ((p.N + 255) / 256);
-    if (p.G == 0 && big * 8 < 5 * (int64_t)num_cus_x8()) variant = 2;
+    if (p.G == 0 && big * 8 < 5 * (int64_t)cus) variant = 2;
     return variant;
 }
 
@@ -1092,6 +1091,19 @@ int gemm_between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool p
     return gemm_skinny_preferred(p, mode, cus) || gemm_shortk_preferred(p, cus) ? kTileDefault : between_tile(p, ct, mode, pow2, cus);
 }
 
+template <class C>
+static bool default_tail_shared(const GemmParams& p, int cus) {
+    const int64_t ntiles = (int64_t)((p.M + C::BM - 1) / C::BM) * ((p.N + C::BN - 1) / C::BN), slots = (int64_t)cus * C::WG_PER_CU;
+    int q_main, q_last, tail_max;
+    return share_bytes<C>(ntiles, slots, p.K / 128, &q_main, &q_last, &tail_max) > 0 && share_default<C>(ntiles, slots, p.K / 128, q_main);
+}
+
+bool gemm_tail_shared(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus) {
+    if (gemm_skinny_preferred(p, mode, cus) || gemm_shortk_preferred(p, cus) || between_tile(p, ct, mode, pow2, cus) != kTileDefault)
+        return false;
+    return default_variant(p, cus) == 0 ? default_tail_shared<Cfg<256, 256, 4, 2, 2>>(p, cus) : default_tail_shared<Cfg<128, 128, 2, 2, 2>>(p, cus);
+}
+
 template <bool POW2>
 static ds3_status launch_between(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int tile, hipStream_t st) {
     // (one round: no tail to share along K)
@@ -1106,8 +1118,8 @@ ds3_status launch_gemm(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, int v
                        hipStream_t st) {
     const bool named = variant >= 0;
     if (!named) {
-        variant = default_variant(p, mode);
         const int cus = num_cus_x8();
+        variant = default_variant(p, cus);
         const bool skinny = p.G == 0 && gemm_skinny_preferred(p, mode, cus);
         const bool shortk = p.G == 0 && !skinny && gemm_shortk_preferred(p, cus);
         const int tile = skinny || shortk ? kTileDefault : between_tile(p, ct, mode, pow2, cus);
@@ -1216,7 +1228,7 @@ ds3_status launch_workspace_init(void* ws, size_t ws_bytes, hipStream_t st) {
 }
 
 size_t gemm_workspace_bytes(const GemmParams& p, ds3_bscale mode, int variant) {
-    if (variant < 0) variant = default_variant(p, mode);
+    if (variant < 0) variant = default_variant(p, num_cus_x8());
     size_t need = 0;
     // the requirement depends on the tile configuration only, not on the output type or the scale kind
     if (launch_variant<false>(p, DS3_BF16, mode, variant, false, nullptr, 0, &need, nullptr) != DS3_OK) return 0;

@@ -93,3 +93,17 @@ def test_between_tile_with_power_of_two_scales(ds3, shape, c_type, mode, tile):
 ])
 def test_dense_one_tile_a_compute_unit(ds3, shape, few, mode):
     assert (ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) >= 0) == few
+
+
+@pytest.mark.parametrize("shape,c_type,mode,pow2,shared", [
+    ((2048, 2048, 2560), 1, 0, 0, 1), ((2048, 2048, 2432), 1, 0, 0, 0),                # 256 tiles of 128x128: 10 and 9 K-steps saved
+    ((1536, 1408, 12416), 0, 1, 0, 1), ((2048, 1152, 4224), 1, 0, 0, 1),               # 132, 144
+    ((1228, 3404, 1152), 1, 0, 0, 0), ((2048, 2176, 2176), 1, 0, 1, 0),                # more than compute units
+    ((2000, 9100, 2048), 0, 1, 0, 1), ((2000, 9100, 1920), 0, 1, 0, 0),                # 288 of 256x256: 8 and 7
+    ((3072, 3072, 1536), 0, 1, 1, 1), ((3072, 3072, 1408), 0, 1, 1, 0),                # 576 of 128x128: 6 and 5
+    ((4096, 4096, 7168), 1, 0, 0, 0), ((4096, 18432, 7168), 1, 0, 0, 0),               # no tail; half of the workgroups
+    ((1333, 3000, 1536), 0, 0, 0, 0), ((8192, 32768, 512), 1, 0, 0, 0), ((32, 18432, 7168), 1, 0, 0, 0),   # other kernels
+    ((0, 2048, 6144), 1, 0, 0, 0), ((2048, 2048, 6100), 1, 0, 0, 0),
+])
+def test_tail_shared(ds3, shape, c_type, mode, pow2, shared):
+    assert ds3._L().ds3_gemm_tail_shared(*shape, mode, c_type, 0, pow2, 256) == shared

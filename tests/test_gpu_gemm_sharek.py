@@ -134,8 +134,8 @@ def test_empty_inner_dimension(ds3):
 
 # a call that names no configuration shares tiles only where the K-steps it saves are worth the exchange
 @pytest.mark.parametrize("shape,variant,shared", [
-    ((2048, 2048, 6144), 2, True), ((2048, 2048, 2048), 2, False), ((1333, 3000, 1536), 2, False),
-    ((2000, 9100, 8192), 0, True), ((2000, 9100, 1024), 0, False),
+    ((2048, 2048, 6144), 2, True), ((2048, 2048, 2048), 2, False), ((2000, 9100, 8192), 0, True), ((2000, 9100, 1024), 0, False),
+    ((2100, 8700, 2304), 0, True), ((1228, 3404, 1152), 2, False),       # a shorter last chunk goes with the full ones
 ])
 def test_default_call_shares_where_it_pays(ds3, shape, variant, shared):
     m, n, k = shape
@@ -146,6 +146,9 @@ def test_default_call_shares_where_it_pays(ds3, shape, variant, shared):
     sb = np.exp(rng.standard_normal(((n + 127) // 128, k // 128))).astype(np.float32)
     args = (dev(a), dev(sa), dev(b), dev(sb))
     assert ds3.ds3_gemm_workspace_bytes(m, n, k) > 0
+    assert ds3._L().ds3_gemm_tail_shared(m, n, k, ds3.DS3_BSCALE_128x128, ds3.DS3_F32, 0, 0, 256) == shared
+    assert ds3._L().ds3_gemm_few_tiles_config(m, n, k, 0, 256) < 0 and ds3._L().ds3_gemm_short_k(m, n, k, 0, 256) == 0
+    assert ds3._L().ds3_gemm_between_tile(m, n, k, 0, ds3.DS3_F32, 0, 256) < 0         # the named tiles, shared or not
     got = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32)
     whole = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32, variant=variant, workspace=None)
     pieces = ds3.ds3_gemm_fp8_bs(*args, out_dtype=torch.float32, variant=variant)
