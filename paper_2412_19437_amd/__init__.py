@@ -37,7 +37,7 @@ SYMBOLS = [
     "ds3_rmsnorm_quant_1x128", "ds3_rmsnorm_quant_1x128_pow2", "ds3_adamw_bf16_states",
     "ds3_quant_act_1x128_e5m6", "ds3_dequant_e5m6",
     "ds3_grouped_gemm_swiglu_quant_fp8_bs", "ds3_grouped_gemm_swiglu_quant_fp8_bs_pow2",
-    "ds3_grouped_gemm_workspace_bytes", "ds3_gemm_few_tiles_config", "ds3_gemm_short_k", "ds3_gemm_between_tile", "ds3_gemm_tail_shared",
+    "ds3_grouped_gemm_workspace_bytes", "ds3_gemm_few_tiles_config", "ds3_gemm_short_k", "ds3_gemm_between_tile", "ds3_gemm_default_kernel", "ds3_gemm_tail_shared",
     "ds3_grouped_gemm_few_rows_tile",
 ]
 
@@ -99,6 +99,7 @@ def _load() -> ctypes.CDLL:
     lib.ds3_gemm_few_tiles_config.argtypes = [i64, i64, i64, i32, i32]
     lib.ds3_gemm_short_k.argtypes = [i64, i64, i64, i32, i32]
     lib.ds3_gemm_between_tile.argtypes = [i64, i64, i64, i32, i32, i32, i32]
+    lib.ds3_gemm_default_kernel.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32]
     lib.ds3_gemm_tail_shared.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32]
     lib.ds3_grouped_gemm_few_rows_tile.argtypes = [i32, i64, i64, i64, i32, i32]
     lib.ds3_gemm_workspace_init.argtypes = [vp, sz, vp]

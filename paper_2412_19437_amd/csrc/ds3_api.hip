@@ -317,15 +317,27 @@ int ds3_gemm_between_tile(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, d
     return gemm_between_tile(p, c_type, sb_mode, pow2 != 0, compute_units);
 }
 
-int ds3_gemm_tail_shared(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int accumulate, int pow2,
-                         int compute_units) {
-    if (M <= 0 || N <= 0 || K <= 0 || K % 128 || M > kMaxDim || N > kMaxDim || K > kMaxDim || compute_units < 8) return 0;
-    GemmParams p{};
+// The parameters of a dense call that the dispatch looks at, with packed operands; false: none such.
+static bool shape_params(GemmParams& p, int64_t M, int64_t N, int64_t K, int accumulate, int compute_units) {
+    if (M <= 0 || N <= 0 || K <= 0 || K % 128 || M > kMaxDim || N > kMaxDim || K > kMaxDim || compute_units < 8) return false;
+    p = GemmParams{};
     p.M = (int)M; p.N = (int)N; p.K = (int)K;
     p.lda = p.ldb = K;
     p.ldc = N;
     p.accumulate = accumulate;
-    return gemm_tail_shared(p, c_type, sb_mode, pow2 != 0, compute_units / 8 * 8);
+    return true;
+}
+
+int ds3_gemm_default_kernel(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int accumulate, int pow2,
+                            int compute_units) {
+    GemmParams p;
+    return shape_params(p, M, N, K, accumulate, compute_units) ? gemm_default_kernel(p, c_type, sb_mode, pow2 != 0, compute_units / 8 * 8) : -1;
+}
+
+int ds3_gemm_tail_shared(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int accumulate, int pow2,
+                         int compute_units) {
+    GemmParams p;
+    return shape_params(p, M, N, K, accumulate, compute_units) && gemm_tail_shared(p, c_type, sb_mode, pow2 != 0, compute_units / 8 * 8);
 }
 
 int ds3_grouped_gemm_few_rows_tile(int32_t G, int64_t total_rows, int64_t N, int64_t K, int swiglu_quant, int compute_units) {

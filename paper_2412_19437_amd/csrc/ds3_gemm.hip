@@ -1091,6 +1091,13 @@ int gemm_between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool p
     return gemm_skinny_preferred(p, mode, cus) || gemm_shortk_preferred(p, cus) ? kTileDefault : between_tile(p, ct, mode, pow2, cus);
 }
 
+int gemm_default_kernel(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus) {
+    if (gemm_skinny_preferred(p, mode, cus)) return DS3_GEMM_KERNEL_FEW + gemm_skinny_config(p, mode, cus);
+    if (gemm_shortk_preferred(p, cus)) return DS3_GEMM_KERNEL_SHORT_K;
+    const int tile = between_tile(p, ct, mode, pow2, cus);
+    return tile != kTileDefault ? DS3_GEMM_KERNEL_BETWEEN + tile : default_variant(p, cus);
+}
+
 template <class C>
 static bool default_tail_shared(const GemmParams& p, int cus) {
     const int64_t ntiles = (int64_t)((p.M + C::BM - 1) / C::BM) * ((p.N + C::BN - 1) / C::BN), slots = (int64_t)cus * C::WG_PER_CU;
@@ -1099,9 +1106,9 @@ static bool default_tail_shared(const GemmParams& p, int cus) {
 }
 
 bool gemm_tail_shared(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus) {
-    if (gemm_skinny_preferred(p, mode, cus) || gemm_shortk_preferred(p, cus) || between_tile(p, ct, mode, pow2, cus) != kTileDefault)
-        return false;
-    return default_variant(p, cus) == 0 ? default_tail_shared<Cfg<256, 256, 4, 2, 2>>(p, cus) : default_tail_shared<Cfg<128, 128, 2, 2, 2>>(p, cus);
+    const int kernel = gemm_default_kernel(p, ct, mode, pow2, cus);
+    if (kernel >= DS3_GEMM_KERNEL_BETWEEN) return false;
+    return kernel == 0 ? default_tail_shared<Cfg<256, 256, 4, 2, 2>>(p, cus) : default_tail_shared<Cfg<128, 128, 2, 2, 2>>(p, cus);
 }
 
 template <bool POW2>

@@ -358,20 +358,37 @@ static ds3_status launch_kb(GemmParams p, ds3_dtype ct, bool rows, int cus, hipS
     return hipGetLastError() == hipSuccess ? DS3_OK : DS3_ERR_LAUNCH;
 }
 
-// Beyond K = 512 the weights don't fit the registers.  A workgroup takes about two steps' time to load its weights: where
-// the main kernel needs no more than one round of its 256x256 tiles and there are few rows to walk, that is not made up
-// for.  Weights and activations from HBM, kernels alone, us, main kernel / this one (240 shapes of 2^21 .. 2^28 outputs,
-// K 128 .. 512): 8192x32768x512 192 / 136, x256 147 / 93; 4096x16384x512 55 / 38; 8192x4096x128 21 / 15; 1320x10976x512
-// 28 / 16; by row, accumulating FP32 18432x7168x512 258 / 193, 4096x7168x512 70 / 52, 15167x440x384 20 / 18.5; at worst
-// 7969x1936x128 12.2 / 13.4, 8192x2048x512 15.3 / 15.9; beyond the line: 453x25312x512 14.1 / 16.6, 163x30416x512 9.3 /
-// 14.2.
+// Beyond K = 512 the weights don't fit the registers.  Up to it the kernel is taken but for
+//   * fewer than 768 rows where the main kernel needs no more than one round of its 256x256 tiles: what a workgroup takes
+//     to load its weights is not made up for (453x25312x512 14.1 us main kernel / 16.6 this one, 163x30416x512 9.3 / 14.2);
+//   * K >= 384 where the main kernel's tiles fill most of one round, and accumulation does not keep it busy: of 128x128
+//     tiles from 5/8 of the round on where the number of column tiles is odd, 3/4 where K = 512 and M < 4096; of 256x256
+//     ones where it is odd and M < 1536.  A workgroup's ranges are then down to two to four steps beside the loading of
+//     its weights, and with an odd number of column tiles a column's workgroups lie on all eight XCDs, each of which
+//     fetches the weights into its own L2 (885x15512x512 1.27 of the main kernel's time, 866x8320x512 10.5 / 13.1);
+//   * accumulation with a last 16-byte piece of a row that is cut, 2^25 outputs and more: the columns beyond the last
+//     whole piece are read and written one by one, and the workgroups that hold them end last (15489x16763x128 460 / 610).
+// Operands from HBM, kernels alone, us: 8192x32768x512 192 / 136, x256 147 / 93; 4096x16384x512 55 / 38; 8192x4096x128
+// 21 / 15; 1320x10976x512 28 / 16; by row, accumulating FP32 18432x7168x512 258 / 193, 4096x7168x512 70 / 52.  25300
+// calls of 2^19 .. 2^28 outputs, every form and alignment of the output, time over the main kernel's: .797, 0.7% of them
+// above 1.03, 1.15 at worst (without the last two exceptions, 1300 calls at .987: .796, 2.5%, 1.53).
 bool gemm_shortk_preferred(const GemmParams& p, int cus) {
     if (p.K > 512) return false;
     // 32-bit byte offsets within a step's rows, and leading dimensions that the main kernel refuses stay refused
     if ((int64_t)257 * p.ldb + p.K >= (1ll << 31) || (int64_t)257 * p.lda + p.K >= (1ll << 31) ||
         (int64_t)33 * p.ldc * 4 >= (1ll << 31) || p.N > (1 << 29) || p.M > (1 << 29))
         return false;
-    return p.M >= 768 || (int64_t)((p.M + 255) / 256) * ((p.N + 255) / 256) > cus;
+    const int64_t tiles_n = (p.N + 255) / 256, large = (int64_t)((p.M + 255) / 256) * tiles_n;
+    if (p.accumulate) {
+        if (p.N % 4 != 0 && (int64_t)p.M * p.N >= (1 << 25)) return false;
+    } else if (p.K >= 384 && large <= cus) {
+        const bool odd = tiles_n % 2 != 0;
+        const int64_t small = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128), slots = 2 * (int64_t)cus;
+        if (large * 8 >= 5 * (int64_t)cus) {             // (the main kernel's choice between its tiles)
+            if (odd && p.M < 1536) return false;
+        } else if (small <= slots && (odd ? 8 * small > 5 * slots : p.K == 512 && p.M < 4096 && 4 * small >= 3 * slots)) return false;
+    }
+    return p.M >= 768 || large > cus;
 }
 
 ds3_status launch_gemm_shortk(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus, hipStream_t st) {

@@ -84,6 +84,8 @@ ds3_status launch_gemm_shortk(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
 // Which of the tiles between the named configurations a dense call takes that names none and is not one of those
 // (see ds3_gemm.hip): 0 .. 2, -1: none of them.
 int gemm_between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus);
+// Which kernel a dense call takes that names no configuration (ds3_gemm_default_kernel's values).
+int gemm_default_kernel(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus);
 // Whether a dense call that names no configuration shares tiles along K where it is given a workspace.
 bool gemm_tail_shared(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int cus);
 // The kernel for few rows, for experts' groups, plain or with SwiGLU and the quantizer behind it: the rows of its tiles,

@@ -107,3 +107,22 @@ def test_dense_one_tile_a_compute_unit(ds3, shape, few, mode):
 ])
 def test_tail_shared(ds3, shape, c_type, mode, pow2, shared):
     assert ds3._L().ds3_gemm_tail_shared(*shape, mode, c_type, 0, pow2, 256) == shared
+
+
+SHORT_K = 16
+
+
+@pytest.mark.parametrize("mode", [BLOCK, ROW])
+@pytest.mark.parametrize("shape,store,accumulate", [
+    ((15489, 16763, 128), True, False), ((15489, 16764, 128), True, True),             # cut columns and a large output
+    ((2049, 16379, 512), True, False), ((2047, 16379, 512), True, True),               # 2^25 outputs
+    ((885, 15512, 512), False, True), ((885, 15360, 512), True, True), ((885, 15512, 256), True, True),    # 61 and 60 column tiles
+    ((1535, 6657, 384), False, True), ((1536, 6657, 384), True, True),                 # 27, 162 tiles of 256x256
+    ((1537, 3328, 512), False, True), ((1536, 3328, 384), True, True), ((1537, 3073, 384), False, True),   # 13 column tiles: 338, 312 and 325 of 128x128
+    ((1536, 4096, 512), False, True), ((1536, 3968, 512), True, True), ((1536, 4096, 384), True, True),    # 16: 384, 372
+    ((4095, 2048, 512), False, True), ((4097, 1800, 512), True, True), ((2048, 4097, 512), True, True),    # 512, 495, 528
+])
+def test_short_k_leaves_to_the_main_kernel(ds3, shape, store, accumulate, mode):
+    f = lambda acc: ds3._L().ds3_gemm_default_kernel(*shape, mode, 0, acc, 0, 256)
+    assert (f(0) == SHORT_K, f(1) == SHORT_K) == (store, accumulate)
+    assert ds3._L().ds3_gemm_short_k(*shape, mode, 256) == store
