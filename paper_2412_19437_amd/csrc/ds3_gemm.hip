@@ -1071,6 +1071,10 @@ static int default_variant(const GemmParams& p, int cus) {
 // 1792x4827x768 1.34 of the former time.  Power-of-two scales (6900 shapes) make the former tiles faster and not these
 // ones' start and end, so two lines lie further out: 192x128 K 1280 .. 2176 .98 (1.29), from 2304 on .87; 256x192 by row
 // for more than two tiles a compute unit, K 1280 .. 2944 .94 (1.21), from 3072 on .85.
+// Accumulation with a cut last piece of a row (N % 4 != 0): its columns are read and written one by one, which the few
+// workgroups of 256x192 tiles spread worse than 128x128 ones do.  Below K = 3072 these calls stay with the latter: 121
+// calls .99 of their time, a third of them above 1.03, 1652x5199x1280 by row 41 / 49 us; from there on 231 calls .89, 1.07 at
+// worst (with whole pieces .82, .92).
 enum { kTileDefault = -1, kTile256x192 = 0, kTile192x128 = 1, kTile192x256 = 2 };      // (weight rows x activation rows)
 static int between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool pow2, int64_t cus) {
     if (p.G > 0) return kTileDefault;
@@ -1082,6 +1086,7 @@ static int between_tile(const GemmParams& p, ds3_dtype ct, ds3_bscale mode, bool
     if (!large && p.K < 1280) return kTileDefault;
     if (large ? tiles(256, 256) <= cus : tiles(128, 128) > 2 * cus) {
         if (ct == DS3_BF16 && !rows && tiles(192, 256) <= cus) return kTile192x256;
+        if (!large && p.accumulate && p.N % 4 != 0 && p.K < 3072) return kTileDefault;
         return tiles(256, 192) <= cus && (large || !rows || !pow2 || p.K >= 3072) ? kTile256x192 : kTileDefault;
     }
     return !large && tiles(128, 128) > cus && tiles(192, 128) <= cus && (rows || !pow2 || p.K >= 2304) ? kTile192x128 : kTileDefault;

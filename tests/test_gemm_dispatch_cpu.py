@@ -126,3 +126,13 @@ def test_short_k_leaves_to_the_main_kernel(ds3, shape, store, accumulate, mode):
     f = lambda acc: ds3._L().ds3_gemm_default_kernel(*shape, mode, 0, acc, 0, 256)
     assert (f(0) == SHORT_K, f(1) == SHORT_K) == (store, accumulate)
     assert ds3._L().ds3_gemm_short_k(*shape, mode, 256) == store
+
+
+@pytest.mark.parametrize("mode", [BLOCK, ROW])
+@pytest.mark.parametrize("shape,tile,accumulating", [
+    ((2305, 3585, 2944), 0, -1), ((2305, 3585, 3072), 0, 0), ((2305, 3588, 2944), 0, 0),      # more than two 128x128 tiles a unit
+    ((2561, 3841, 640), 0, 0), ((2050, 2001, 2432), 1, 1),        # the other tiles lose nothing by it
+])
+def test_between_tile_of_an_accumulating_call(ds3, shape, tile, accumulating, mode):
+    f = lambda acc: ds3._L().ds3_gemm_default_kernel(*shape, mode, 0, acc, 0, 256)
+    assert (f(0), f(1)) == (8 + tile, 2 if accumulating < 0 else 8 + accumulating)
