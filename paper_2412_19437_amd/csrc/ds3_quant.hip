@@ -668,12 +668,14 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_kernel(
     }
 }
 
-// Rows of up to 2048 elements: one WAVE per row.  A workgroup per row has at most a quarter of the granules a lane could
+// Narrow rows (up to 2048 elements): one WAVE per row.  A workgroup per row has at most a quarter of the granules a lane could
 // hold, and the row's chain (load, sum, barrier, root, scale, cast) bounds it.  Here granule i of a lane is what wave i of
 // that workgroup would hold, and the granules' sums are kept apart until they meet in the same order, so the result is
 // the same bit for bit; there is no barrier.  8192 rows, us, workgroup / wave: 512 15.5 / 6.5 (the launch and one
 // latency), 1024 17.6 / 8.4, 1536 19.5 / 11.6, 2048 21.4 / 14.2 (3.5 TB/s); with eight granules 3072 25.4 / 26.2, 4096 30.0 /
-// 32.5, so wider rows stay with the workgroup.
+// 32.5, so wider rows stay with the workgroup.  So do fewer than 1024 rows of more than 1024 elements: a wave's four
+// granules one after another take longer than the barrier between four waves while compute units are idle (32 rows 3.6 /
+// 4.1, 256 rows 3.9 / 4.5; 512 rows 4.5 / 4.7, 1024 rows 6.0 / 5.4).
 template <int G>
 __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_narrow_kernel(
     const uint8_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx_bytes, const float* __restrict__ gamma,
@@ -958,7 +960,7 @@ ds3_status launch_rmsnorm_quant_1x128(const void* x, int64_t rows, int64_t cols,
     if (cols > (int64_t)kNormMaxGranules * 2048) return DS3_ERR_UNSUPPORTED;
     // four workgroups per compute unit (all resident at once), each walking rows a grid apart
     const int64_t grid = rows < 1024 ? rows : 1024;
-    if (cols <= 2048) {
+    if (cols <= 1024 || (cols <= 2048 && rows >= 1024)) {
         const dim3 narrow((unsigned)(rows < 8192 ? (rows + 3) / 4 : 2048));      // eight workgroups per compute unit
         auto run = [&](auto kernel) {
             kernel<<<narrow, 256, 0, st>>>((const uint8_t*)x, rows, cols, ldx * 2, gamma, eps, (uint8_t*)y, ldy * 2, q, ldq, s, ssr, ssk, pow2);

@@ -251,7 +251,9 @@ def test_e5m6_device_rounding_on_every_code_and_tie(ds3):
 
 
 @pytest.mark.parametrize("pow2", [False, True])
-@pytest.mark.parametrize("shape", [(1, 8), (5, 128), (3, 504), (6, 512), (7, 520), (4, 1024), (5, 1032), (4, 2048), (3, 2056), (8197, 264)])
+@pytest.mark.parametrize("shape", [(1, 8), (5, 128), (3, 504), (6, 512), (7, 520), (4, 1024), (5, 1032), (4, 2048), (3, 2056), (8197, 264),
+                                   (1023, 1032), (1024, 1032), (1031, 1544), (1024, 2048), (1024, 2056)])
 def test_rmsnorm_of_narrow_rows(ds3, shape, pow2):
-    """A wave per row up to 2048 columns: every number of granules, partly filled ones, more rows than the grid holds."""
+    """A wave per row up to 1024 columns, from 1024 rows on up to 2048: every number of granules, partly filled ones, more
+    rows than the grid holds, both sides of the lines."""
     test_rmsnorm_fused_with_quantizer(ds3, shape, pow2)
