@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 # the first leaves a partial round of tiles, which the GEMM shares along K through the workspace: the arrival counters
 # are updated by every replay and left ready for the next; the second runs the kernel for few tiles
-@pytest.mark.parametrize("shape,shared", [((1408, 3072, 1024), True), ((384, 640, 1024), False)])
+@pytest.mark.parametrize("shape,shared", [((2048, 1152, 4224), True), ((384, 640, 1024), False)])
 def test_quantize_and_gemm_in_a_captured_graph(ds3, shape, shared):
     announce(f"graph capture {shape}")
     L = ds3._L()
@@ -27,6 +27,7 @@ def test_quantize_and_gemm_in_a_captured_graph(ds3, shape, shared):
     sb = torch.empty((N // 128, K // 128), dtype=torch.float32, device=x.device)
     y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     assert (L.ds3_gemm_few_tiles_config(M, N, K, ds3.DS3_BSCALE_128x128, 256) < 0) == shared
+    assert L.ds3_gemm_tail_shared(M, N, K, ds3.DS3_BSCALE_128x128, ds3.DS3_BF16, 0, 0, 256) == shared
     ws_bytes = ds3.ds3_gemm_workspace_bytes(M, N, K)
     assert ws_bytes > 0
     ws = ds3.new_gemm_workspace(ws_bytes, x.device)     # prepared once, outside the graph

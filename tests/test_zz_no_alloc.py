@@ -19,21 +19,30 @@ def _rand_codes(rng, shape):
 
 def test_no_alloc_entry_point_matches_the_workspace_entry_point(ds3):
     rng = np.random.default_rng(91)
-    # the first two share tail tiles along K (144 and 264 tiles of 128 x 128), the others run the kernel for few tiles
-    for (m, n, k, shared) in [(2048, 1152, 4224, True), (1333, 3000, 1536, True), (2048, 1536, 2048, False), (384, 640, 1024, False)]:
+    # the named variant whose tail tiles the first three share along K (144 and 256 tiles of 128 x 128, 288 of 256 x 256);
+    # the others share nothing: tiles between the named sizes, and the kernel for few tiles
+    for (m, n, k, shared) in [(2048, 1152, 4224, 2), (2048, 2048, 2560, 2), (2000, 9100, 2048, 0), (1333, 3000, 1536, None),
+                              (2048, 1536, 2048, None), (384, 640, 1024, None)]:
         announce(f"no-alloc GEMM {m}x{n}x{k}")
-        assert (ds3._L().ds3_gemm_few_tiles_config(m, n, k, ds3.DS3_BSCALE_128x128, 256) < 0) == shared
+        for ct in (ds3.DS3_F32, ds3.DS3_BF16):
+            assert ds3._L().ds3_gemm_tail_shared(m, n, k, ds3.DS3_BSCALE_128x128, ct, 0, 0, 256) == (shared is not None)
         assert ds3.ds3_gemm_workspace_bytes(m, n, k) > 0
         a, b = _rand_codes(rng, (m, k)), _rand_codes(rng, (n, k))
         sa = np.exp(rng.standard_normal((m, k // 128))).astype(np.float32)
         sb = np.exp(rng.standard_normal(((n + 127) // 128, k // 128))).astype(np.float32)
         ad, sad, bd, sbd = dev(a), dev(sa), dev(b), dev(sb)
+        ref = orc.gemm_fp8_bs(a, sa, b, sb)
         for dt, tol in ((torch.bfloat16, 2e-3), (torch.float32, 1e-4)):
             want = ds3.ds3_gemm_fp8_bs(ad, sad, bd, sbd, out_dtype=dt)       # caller's workspace (from the binding's cache)
             got = torch.full((m, n), 3.0, dtype=dt, device="cuda:0")
             ds3.ds3_gemm_fp8_bs_noalloc(ad, sad, bd, sbd, got)
             assert torch.equal(got, want), (m, n, k, dt)
-            assert normwise(host(got), orc.gemm_fp8_bs(a, sa, b, sb)) <= tol
+            assert normwise(host(got), ref) <= tol
+        # (the loop ends on FP32, where the order of the sums shows: the entry point did share, or did not)
+        whole = ds3.ds3_gemm_fp8_bs(ad, sad, bd, sbd, out_dtype=torch.float32, workspace=None)
+        assert torch.equal(got, whole) == (shared is None)
+        if shared is not None:
+            assert torch.equal(got, ds3.ds3_gemm_fp8_bs(ad, sad, bd, sbd, out_dtype=torch.float32, variant=shared))
         # accumulation into FP32, and a second call right behind the first on the same array
         acc = torch.zeros((m, n), dtype=torch.float32, device="cuda:0")
         ds3.ds3_gemm_fp8_bs_noalloc(ad, sad, bd, sbd, acc, accumulate=True)
