@@ -300,7 +300,9 @@ int ds3_gemm_tail_share_steps(int tail_tiles, int k_steps, int workgroups);
 /*
  * Host logic of the dispatch, exported for its test (no GPU work): which configuration of the kernel for
  * few rows or few tiles a dense call that names no variant takes on a device of `compute_units`, or -1 where
- * another kernel takes it.  (Rows as long as K; longer ones may be left to the main kernel.)
+ * another kernel takes it (0 .. 4: tiles ranked by their time; then one tile a compute unit: 5 .. 8 of 48, 64, 80 and 96
+ * weight rows up to 32 activation rows, 9, 11 and 12 of 48, 80 and 96 up to 64, 13 .. 15 of 80, 96 and 112 up to 128;
+ * 16: number 4's tile and two groups of waves).  (Rows as long as K; longer ones may be left to the main kernel.)
  */
 int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
 /* ... whether one that does not accumulate takes the kernel for a short K and a large output (1 or 0), */

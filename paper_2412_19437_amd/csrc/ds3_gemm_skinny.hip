@@ -376,8 +376,23 @@ static int one_tile_waves(int M, int N, int K, int cus) {
     return M <= 128 && w >= 5 && w <= 7 && K >= 1280 ? w : 0;
 }
 
+// One 128x64 tile a compute unit at most: there is room for a second group of waves, and twice the bytes in flight.  4000
+// shapes of 129 to 256 tiles, time over that of one group: K 1024 .. 10112 .89, by row .87 (1.02 at worst; 768x1536x7168
+// 30.8 / 24.6 us, 1024x2048x7168 31.7 / 29.4, by row 768x1536x8192 38 / 30); below .93 (1.08).  One group and six stages
+// instead 1.03.
+static bool two_groups(int M, int N, int K, int cus) {
+    return M > 64 && K >= 1024 && (int64_t)((M + 63) / 64) * ((N + 127) / 128) <= cus;
+}
+
+// The configuration's number: the ranked ones' index, then the ones taken aside.  Up to 64 rows the one of 64 weight rows
+// is number 3 itself.
+enum { kOneTile32 = kSkinnyCfgs, kOneTile64 = kOneTile32 + 4, kOneTile128 = kOneTile64 + 4, kTwoGroups = kOneTile128 + 3 };
 static int skinny_choice(int M, int N, int K, int cus) {
-    if (one_tile_waves(M, N, K, cus)) return M <= 32 ? 2 : 4;
+    if (const int w = one_tile_waves(M, N, K, cus)) {
+        if (M <= 32) return kOneTile32 + w - 3;
+        if (M <= 64) return w == 4 ? 3 : kOneTile64 + w - 3;
+        return kOneTile128 + w - 5;
+    }
     int best = 0;
     float best_us = 0.f;
     for (int i = 0; i < kSkinnyCfgs; ++i) {
@@ -389,17 +404,17 @@ static int skinny_choice(int M, int N, int K, int cus) {
         if (rest) us += steps * (c.alone + (c.full - c.alone) * ((float)rest / (float)slots)) + c.out;
         if (i == 0 || us < best_us) { best = i; best_us = us; }
     }
-    return best;
+    return best == 4 && two_groups(M, N, K, cus) ? kTwoGroups : best;
 }
 
 // Up to 64 rows (nothing is gained from a second row tile: 64x32768x3072 37 -> 26 us), or fewer 128x128 tiles than
 // compute units, as far as K lets them (and what `one_tile_waves` takes aside).  While every compute unit has at most
-// one of this kernel's 64x128 tiles, a K-step of it is shorter than the main kernel's for a tile twice as high.  With a second one it is not: the two tiles
-// move 1.5 times the bytes through LDS, and only the shorter start and end of a tile are left to gain, which a short K
-// shows and a long one does not; the rescale by row costs this kernel more than the main one.  Weights from HBM,
-// kernels alone, us, main kernel / this one, at the worst of the shapes measured beside each line (1600 shapes in four
-// forms, M up to 16384, K 128 .. 18432; within the lines the worst is 1.003 of the main kernel's time, 1.03 on 900
-// others that the lines were not drawn from; beyond them 1.56):
+// one of this kernel's 64x128 tiles, a K-step of it is shorter than the main kernel's for a tile twice as high.  With a
+// second one it is not: the two tiles move 1.5 times the bytes through LDS, and only the shorter start and end of a tile
+// are left to gain, which a short K shows and a long one does not; the rescale by row costs this kernel more than the
+// main one.  Weights from HBM, kernels alone, us, main kernel / this one, at the worst of the shapes measured beside each
+// line (1600 shapes in four forms, M up to 16384, K 128 .. 18432; within the lines the worst is 1.003 of the main
+// kernel's time, 1.03 on 900 others that the lines were not drawn from; beyond them 1.56):
 //   tiles <= half the compute units   8192x128x18432 by row 103 / 68
 //   tiles <= compute units            385x3392x12288 by row 69 / 68; beyond: 16384x128x18432 by row 111 / 117
 //   more                              1457x2275x4096 34 / 33, by row 4933x444x3072 34 / 34, 552x4096x256 19 / 12;
@@ -429,38 +444,21 @@ ds3_status launch_gemm_skinny(const GemmParams& p, ds3_dtype ct, ds3_bscale mode
     switch (skinny_choice(p.M, p.N, p.K, cus)) {
         case 0: return launch_cfg<SkinnyCfg<1, 2, 2, 4, 4>>(p, ct, rows, pow2, st);
         case 1: return launch_cfg<SkinnyCfg<1, 2, 2, 2, 4>>(p, ct, rows, pow2, st);
-        case 2:
-            switch (one_tile_waves(p.M, p.N, p.K, cus)) {
-                case 3: return launch_cfg<SkinnyCfg<1, 2, 3, 2, 5>>(p, ct, rows, pow2, st);
-                case 4: return launch_cfg<SkinnyCfg<1, 2, 4, 2, 5>>(p, ct, rows, pow2, st);
-                case 5: return launch_cfg<SkinnyCfg<1, 2, 5, 2, 4>>(p, ct, rows, pow2, st);
-                case 6: return launch_cfg<SkinnyCfg<1, 2, 6, 1, 6>>(p, ct, rows, pow2, st);
-                default: return launch_cfg<SkinnyCfg<2, 2, 4, 2, 3>>(p, ct, rows, pow2, st);
-            }
+        case 2: return launch_cfg<SkinnyCfg<2, 2, 4, 2, 3>>(p, ct, rows, pow2, st);
         case 3: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
-        default:
-            if (p.M > 64) {
-                switch (one_tile_waves(p.M, p.N, p.K, cus)) {
-                    case 5: return launch_cfg<SkinnyCfg<1, 8, 5, 1, 5>>(p, ct, rows, pow2, st);
-                    case 6: return launch_cfg<SkinnyCfg<1, 8, 6, 1, 4>>(p, ct, rows, pow2, st);
-                    case 7: return launch_cfg<SkinnyCfg<1, 8, 7, 1, 4>>(p, ct, rows, pow2, st);
-                    default: break;
-                }
-                // One 128x64 tile a compute unit at most: there is room for a second group of waves, and twice the bytes in
-                // flight.  4000 shapes of 129 to 256 tiles, time over that of one group: K 1024 .. 10112 .89, by row .87
-                // (1.02 at worst; 768x1536x7168 30.8 / 24.6 us, 1024x2048x7168 31.7 / 29.4, by row 768x1536x8192 38 / 30);
-                // below .93 (1.08).  One group and six stages instead 1.03.
-                if (p.K >= 1024 && (int64_t)((p.M + 63) / 64) * ((p.N + 127) / 128) <= cus)
-                    return launch_cfg<SkinnyCfg<2, 4, 4, 2, 3>>(p, ct, rows, pow2, st);
-                return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
-            }
-            switch (one_tile_waves(p.M, p.N, p.K, cus)) {
-                case 3: return launch_cfg<SkinnyCfg<1, 4, 3, 2, 4>>(p, ct, rows, pow2, st);
-                case 4: return launch_cfg<SkinnyCfg<1, 4, 4, 2, 4>>(p, ct, rows, pow2, st);
-                case 5: return launch_cfg<SkinnyCfg<1, 4, 5, 2, 3>>(p, ct, rows, pow2, st);
-                case 6: return launch_cfg<SkinnyCfg<1, 4, 6, 1, 5>>(p, ct, rows, pow2, st);
-                default: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
-            }
+        case 4: return launch_cfg<SkinnyCfg<2, 4, 4, 1, 3>>(p, ct, rows, pow2, st);
+        case kOneTile32 + 0: return launch_cfg<SkinnyCfg<1, 2, 3, 2, 5>>(p, ct, rows, pow2, st);
+        case kOneTile32 + 1: return launch_cfg<SkinnyCfg<1, 2, 4, 2, 5>>(p, ct, rows, pow2, st);
+        case kOneTile32 + 2: return launch_cfg<SkinnyCfg<1, 2, 5, 2, 4>>(p, ct, rows, pow2, st);
+        case kOneTile32 + 3: return launch_cfg<SkinnyCfg<1, 2, 6, 1, 6>>(p, ct, rows, pow2, st);
+        case kOneTile64 + 0: return launch_cfg<SkinnyCfg<1, 4, 3, 2, 4>>(p, ct, rows, pow2, st);
+        case kOneTile64 + 2: return launch_cfg<SkinnyCfg<1, 4, 5, 2, 3>>(p, ct, rows, pow2, st);
+        case kOneTile64 + 3: return launch_cfg<SkinnyCfg<1, 4, 6, 1, 5>>(p, ct, rows, pow2, st);
+        case kOneTile128 + 0: return launch_cfg<SkinnyCfg<1, 8, 5, 1, 5>>(p, ct, rows, pow2, st);
+        case kOneTile128 + 1: return launch_cfg<SkinnyCfg<1, 8, 6, 1, 4>>(p, ct, rows, pow2, st);
+        case kOneTile128 + 2: return launch_cfg<SkinnyCfg<1, 8, 7, 1, 4>>(p, ct, rows, pow2, st);
+        case kTwoGroups: return launch_cfg<SkinnyCfg<2, 4, 4, 2, 3>>(p, ct, rows, pow2, st);
+        default: return DS3_ERR_UNSUPPORTED;            // (not reached)
     }
 }
 

@@ -44,10 +44,17 @@ def test_grouped(ds3, call, tile):
 
 
 def test_the_gpu_tests_reach_every_configuration(ds3):
-    """The shapes that the kernel's own tests run, which name no variant."""
+    """The shapes that the kernel's own tests run, which name no variant: every configuration, its ring of stages wrapped."""
     for mode in (BLOCK, ROW):
-        taken = [ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) for shape in dense_tests.SHAPES]
-        assert min(taken) >= 0 and set(taken) == set(range(5)), mode
+        config = lambda shapes: [ds3._L().ds3_gemm_few_tiles_config(*shape, mode, 256) for shape in shapes]
+        assert min(config(dense_tests.SHAPES)) >= 0
+        assert set(config(dense_tests.SHAPES + dense_tests.ONE_TILE)) == set(range(17)) - {10}, mode       # (10 would be 3)
+        steps = {c: [s[2] // 128 for s in dense_tests.SHAPES + dense_tests.ONE_TILE if config([s])[0] == c] for c in range(17)}
+        # (steps of a stage, stages): each configuration's ring of stages wraps, and K-steps are left over where they are split
+        split = {0: (4, 4), 1: (2, 4), 2: (2, 3), 3: (2, 4), 4: (1, 3), 5: (2, 5), 6: (2, 5), 7: (2, 4), 8: (1, 6), 9: (2, 4), 11: (2, 3),
+                 12: (1, 5), 13: (1, 5), 14: (1, 4), 15: (1, 4), 16: (2, 3)}
+        for c, (wk, ns) in split.items():
+            assert any(-(-k // wk) > ns for k in steps[c]) and (wk == 1 or any(k % wk for k in steps[c])), (mode, c, steps[c])
     tile = ds3._L().ds3_grouped_gemm_few_rows_tile
     groups = grouped_tests.GROUPS
     plain = {tile(len(groups[g]), sum(groups[g]) + 3, n, k, 0, 256) for g, n, k in grouped_tests.PLAIN}
