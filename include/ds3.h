@@ -140,10 +140,12 @@ ds3_status ds3_quant_w_128x128(const void* w, ds3_dtype wt, int64_t n, int64_t k
  * in K order by whichever workgroup completes a tile (Section 3.3.2 leaves the
  * order of the FP32 additions open).  Pass ds3_gemm_workspace_bytes() bytes to
  * allow it, or NULL (with any size) to forbid it; a non-NULL workspace that is
- * too small is DS3_ERR_WORKSPACE.  (Calls of few rows or few tiles divide K inside
- * a workgroup instead and leave the workspace alone.)  Results are deterministic for a given shape
- * and workspace choice, but not bit-comparable across shapes or between a
- * call with and a call without workspace.
+ * too small is DS3_ERR_WORKSPACE, also where the call would leave it alone: calls of
+ * few rows or few tiles (which divide K inside a workgroup instead), of a short K, of
+ * tiles that all run in one round, and those for which sharing does not pay do
+ * (ds3_gemm_tail_shared answers for a shape).  Results are deterministic for a given
+ * shape and workspace choice, but not bit-comparable across shapes or between a call
+ * with and a call without workspace.
  */
 ds3_status ds3_gemm_fp8_bs(int64_t M, int64_t N, int64_t K,
                            const uint8_t* a, int64_t lda,
@@ -264,10 +266,12 @@ ds3_status ds3_grouped_gemm_fp8_bs_pow2(int variant, int32_t G, const int32_t* g
                                         void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * Bytes of device workspace with which ds3_gemm_fp8_bs / _pow2 share tail tiles
- * along K for this shape (the larger of the two scale modes' needs; 0: the call
- * would not use a workspace).  The _v form answers for one tile configuration
- * and scale mode (variant -1: the default choice).
+ * Bytes of device workspace that a call of this shape has to be given, if any: what
+ * the tail tiles of the variant that it starts from would need if they were shared
+ * along K (the larger of the two scale modes' needs; 0: nothing to share).  For calls
+ * that name no variant this is an upper bound: those listed at ds3_gemm_fp8_bs leave
+ * the workspace alone, and lose nothing with NULL instead.  The _v form answers for one
+ * tile configuration and scale mode (variant -1: the default choice).
  * The grouped calls use a workspace of ds3_grouped_gemm_workspace_bytes() bytes
  * (a few counters, any shape): with it the tiles beyond each workgroup's first
  * are handed out through a queue, so workgroups that drew tiles with few valid
