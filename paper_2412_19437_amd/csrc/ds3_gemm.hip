@@ -880,6 +880,8 @@ __global__ __launch_bounds__(C::NT) void gemm_fp8_bs_kernel(const GemmParams p) 
                         const int64_t grow = cur.m0 + ml;
                         const u32x2 cw = {cvt4_e4m3(bf16_lo(w[0]) * gs.r, bf16_hi(w[0]) * gs.r, bf16_lo(w[1]) * gs.r, bf16_hi(w[1]) * gs.r),
                                           cvt4_e4m3(bf16_lo(w[2]) * gs.r, bf16_hi(w[2]) * gs.r, bf16_lo(w[3]) * gs.r, bf16_hi(w[3]) * gs.r)};
+                        // (plain stores, as the stand-alone producers have, change nothing here: 532.7 / 532.5 us the expert
+                        // FFN of 8192 rows, whose down product reads these 17 MB of codes)
                         __builtin_nontemporal_store(cw, reinterpret_cast<u32x2*>(p.q_out + grow * p.ldq + ob * 128 + lane16 * 8));
                         if (lane16 == 0) p.s_out[grow * p.sor + ob * p.sok] = gs.s;
                     }
@@ -1058,11 +1060,12 @@ static int default_variant(const GemmParams& p, int cus) {
 }
 
 // Tiles between those sizes, for dense calls that name no configuration and leave the chip unevenly filled: all tiles in
-// ONE round, each a quarter smaller than what the call would run with.  Where 256x256 tiles fill 160 to 256 compute
-// units, 192x256 tiles (12 waves of 64x64; BF16 output and block scales only, other outputs spill) or 256x192 ones that
-// still fit one each take three quarters of the time; where there are more 128x128 tiles than compute units, some hold
-// two of them and the others wait, and 192x128 tiles (12 waves of 64x32, three stages) or, beyond two each, the former
-// are all resident at once.  Up to K = 1152 the two smaller tiles' start and end still hide behind each other.
+// ONE round, each a quarter smaller than what the call would run with.
+//   256x256 tiles that fill 160 to 256 compute units: 192x256 ones (12 waves of 64x64; BF16 output and block scales only,
+//   other outputs spill in the K-loop), else 256x192 ones, where these still fit one each.
+//   More than two 128x128 tiles a compute unit: the same; more than one, so that some hold two and the others wait: 192x128
+//   ones (12 waves of 64x32, three stages; FP32 output by row spills eight registers, outside the K-loop).  From K = 1280 on:
+//   up to there the two smaller tiles' start and end still hide behind each other.
 // 2800 shapes (200 to 750 tiles of 128x128, K 640 .. 10112), BF16 / FP32 / accumulating by row, time over the former
 // choice's, geometric mean (worst): 256x256 replaced .83 (.96) / .88 (.97) / .83 (.92); more than two 128x128 tiles a
 // compute unit .75 (.92) / .76 (.90) / .88 (1.05); more than one .88 (1.08) / .84 (.98) / .86 (1.01).  us: 8192x576x7168

@@ -7,8 +7,9 @@
 // and the activation rows stream past, 32 at a time, through a ring of LDS stages.  Every 32 rows a wave has 32 x 64
 // finished sums, and they leave while the next rows are multiplied; two workgroups of four waves share a compute unit,
 // so that one's barrier is the other's work (8192 x 32768 x 512, BF16 output: 192 -> 136 us, power-of-two scales 172 ->
-// 125; the products alone take 106 us at the rate of the largest dense calls, the stores alone 94).  Per activation fragment read from LDS a wave issues four products (the
-// main kernel's eight need a weight fragment each on top).
+// 125; the products alone take 106 us at the rate of the largest dense calls, the stores alone 94).  Per activation
+// fragment read from LDS a wave issues four products (the main kernel's eight need a weight fragment each on top).
+// Only FP32 output by row with K = 512 does not fit the registers (one is spilled).
 //
 // The workgroups that run together cover whole rows of the output: neighbouring workgroups write neighbouring
 // columns (8192 x 32768 BF16, stores alone: 94 us in this order, 101-135 us with an XCD's workgroups side by side, 105-113
@@ -326,8 +327,10 @@ __global__ __launch_bounds__(256, 2) void gemm_shortk_kernel(const GemmParams p,
 }
 
 // ---- host side -------------------------------------------------------------------
-// Ranges of rows per column tile: the rounds of workgroups that there are, each its steps and what loading its weights
-// takes (about six steps' time).
+// Ranges of rows per column tile: the rounds of workgroups that there are, each its steps and what comes before them, counted
+// as six steps.  (Measured over 9800 calls of one round, the launch and the loading of the weights take 3 us at K 128 and
+// 4 to 6 at K 512, a step 1.5 to 2.2 us with BF16 output, 2.9 to 3.3 with FP32, 5.5 to 6 accumulating: two or three steps
+// rather than six.  The count only matters where several rounds compete, and favours few.)
 static int short_splits(int64_t tiles_n, int64_t steps, int64_t slots) {
     int best = 1;
     int64_t best_cost = 0;

@@ -24,7 +24,9 @@ __device__ __forceinline__ void st_stream(uint8_t* p, V v) {
 // 617 us a step where plain stores of the new weights take 633).  Codes are: the GEMM behind a fused
 // producer finds them in the memory-side cache where they went there by plain stores (8192 x 7168
 // behind RMSNorm, N 576: the GEMM 56 -> 42 us, the producer's time the same; SwiGLU and a 4096 x 7168 x
-// 18432 product 484 -> 477 us).  The plain quantizers and the transposing kernels are 5-15% slower with it.
+// 18432 power-of-two product 484 -> 477 us.  Behind SwiGLU it is a small thing: the producer alone takes
+// .96 to 1.05 of its time with plain stores, it and the GEMM .975 to 1.02, 14 shapes, mean .999).  The plain
+// quantizers and the transposing kernels are 5-15% slower with non-temporal stores.
 template <typename V>
 __device__ __forceinline__ void st_nt(uint8_t* p, V v) {
     __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
@@ -675,7 +677,8 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_kernel(
 // latency), 1024 17.6 / 8.4, 1536 19.5 / 11.6, 2048 21.4 / 14.2 (3.5 TB/s); with eight granules 3072 25.4 / 26.2, 4096 30.0 /
 // 32.5, so wider rows stay with the workgroup.  So do fewer than 1024 rows of more than 1024 elements: a wave's four
 // granules one after another take longer than the barrier between four waves while compute units are idle (32 rows 3.6 /
-// 4.1, 256 rows 3.9 / 4.5; 512 rows 4.5 / 4.7, 1024 rows 6.0 / 5.4).
+// 4.1, 256 rows 3.9 / 4.5; 512 rows 4.5 / 4.7, 1024 rows 6.0 / 5.4).  With two granules it is even there (.96 of the time
+// with rows in the caches, 1.04 from HBM).
 template <int G>
 __global__ __launch_bounds__(256) void rmsnorm_quant_1x128_narrow_kernel(
     const uint8_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx_bytes, const float* __restrict__ gamma,
