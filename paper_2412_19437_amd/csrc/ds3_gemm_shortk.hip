@@ -327,8 +327,8 @@ __global__ __launch_bounds__(256, 2) void gemm_shortk_kernel(const GemmParams p,
 }
 
 // ---- host side -------------------------------------------------------------------
-// Ranges of rows per column tile: the rounds of workgroups that there are, each its steps and what comes before them, counted
-// as six steps.  (Measured over 9800 calls of one round, the launch and the loading of the weights take 3 us at K 128 and
+// Ranges of rows per column tile: the rounds of workgroups that there are, each its steps and what comes before them,
+// counted as six steps.  (Measured over 9800 calls of one round, the launch and the loading of the weights take 3 us at K 128 and
 // 4 to 6 at K 512, a step 1.5 to 2.2 us with BF16 output, 2.9 to 3.3 with FP32, 5.5 to 6 accumulating: two or three steps
 // rather than six.  The count only matters where several rounds compete, and favours few.)
 static int short_splits(int64_t tiles_n, int64_t steps, int64_t slots) {
@@ -364,17 +364,19 @@ static ds3_status launch_kb(GemmParams p, ds3_dtype ct, bool rows, int cus, hipS
 // Beyond K = 512 the weights don't fit the registers.  Up to it the kernel is taken but for
 //   * fewer than 768 rows where the main kernel needs no more than one round of its 256x256 tiles: what a workgroup takes
 //     to load its weights is not made up for (453x25312x512 14.1 us main kernel / 16.6 this one, 163x30416x512 9.3 / 14.2);
-//   * K >= 384 where the main kernel's tiles fill most of one round, and accumulation does not keep it busy: of 128x128
-//     tiles from 5/8 of the round on where the number of column tiles is odd, 3/4 where K = 512 and M < 4096; of 256x256
-//     ones where it is odd and M < 1536.  A workgroup's ranges are then down to two to four steps beside the loading of
-//     its weights, and with an odd number of column tiles a column's workgroups lie on all eight XCDs, each of which
-//     fetches the weights into its own L2 (885x15512x512 1.27 of the main kernel's time, 866x8320x512 10.5 / 13.1);
-//   * accumulation with a last 16-byte piece of a row that is cut, 2^25 outputs and more: the columns beyond the last
-//     whole piece are read and written one by one, and the workgroups that hold them end last (15489x16763x128 460 / 610).
+//   * one round of the main kernel's tiles, and 1.5 MiB of weights or more for an XCD to fetch behind 128x128 tiles, 4 MiB
+//     behind 256x256 ones.  A workgroup's ranges are then down to two to four steps.  The workgroups are dealt to the eight
+//     XCDs in turn, so a column tile's lie on 8 / gcd(column tiles, 8) of them, each of which loads the weights into its
+//     own L2: with 33 column tiles all XCDs load all weights (866x8320x512 10.5 us main kernel / 13.1 this one), with 32
+//     an eighth each.  (Where rows end within a 16-byte piece the main kernel's epilogue is the slower one: 2048x2687x384
+//     12.9 / 8.8.);
+//   * accumulation with a last 16-byte piece of a row that is cut, outputs times columns of that piece from 7 * 2^24 on:
+//     these columns are read and written one by one, and the workgroups that hold them end last, the later the more steps
+//     they have (15489x16763x128 460 / 610; 9567x3626x512 120 / 89).
 // Operands from HBM, kernels alone, us: 8192x32768x512 192 / 136, x256 147 / 93; 4096x16384x512 55 / 38; 8192x4096x128
 // 21 / 15; 1320x10976x512 28 / 16; by row, accumulating FP32 18432x7168x512 258 / 193, 4096x7168x512 70 / 52.  25300
-// calls of 2^19 .. 2^28 outputs, every form and alignment of the output, time over the main kernel's: .797, 0.7% of them
-// above 1.03, 1.15 at worst (without the last two exceptions, 1300 calls at .987: .796, 2.5%, 1.53).
+// calls of 2^19 .. 2^28 outputs, every form and alignment of the output, time over the main kernel's: .795, 1.1% of them
+// above 1.03, 1.24 at worst (without the last two exceptions, 570 calls at 1.06: .796, 2.5%, 1.53).
 bool gemm_shortk_preferred(const GemmParams& p, int cus) {
     if (p.K > 512) return false;
     // 32-bit byte offsets within a step's rows, and leading dimensions that the main kernel refuses stay refused
@@ -383,13 +385,12 @@ bool gemm_shortk_preferred(const GemmParams& p, int cus) {
         return false;
     const int64_t tiles_n = (p.N + 255) / 256, large = (int64_t)((p.M + 255) / 256) * tiles_n;
     if (p.accumulate) {
-        if (p.N % 4 != 0 && (int64_t)p.M * p.N >= (1 << 25)) return false;
-    } else if (p.K >= 384 && large <= cus) {
-        const bool odd = tiles_n % 2 != 0;
-        const int64_t small = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128), slots = 2 * (int64_t)cus;
-        if (large * 8 >= 5 * (int64_t)cus) {             // (the main kernel's choice between its tiles)
-            if (odd && p.M < 1536) return false;
-        } else if (small <= slots && (odd ? 8 * small > 5 * slots : p.K == 512 && p.M < 4096 && 4 * small >= 3 * slots)) return false;
+        if ((int64_t)p.M * p.N * (p.N % 4) >= (7 << 24)) return false;
+    } else if (large <= cus && p.N % 8 == 0) {
+        int64_t weights = (int64_t)p.N * p.K;            // bytes an XCD fetches
+        for (int f = 2; f <= 8 && tiles_n % f == 0; f *= 2) weights /= 2;
+        const int64_t small = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
+        if (large * 8 >= 5 * (int64_t)cus ? weights >= 4 << 20 : small <= 2 * (int64_t)cus && weights >= 3 << 19) return false;
     }
     return p.M >= 768 || large > cus;
 }

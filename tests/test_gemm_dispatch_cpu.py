@@ -122,12 +122,13 @@ SHORT_K = 16
 @pytest.mark.parametrize("mode", [BLOCK, ROW])
 @pytest.mark.parametrize("shape,store,accumulate", [
     ((15489, 16763, 128), True, False), ((15489, 16764, 128), True, True),             # cut columns and a large output
-    ((2049, 16379, 512), True, False), ((2047, 16379, 512), True, True),               # 2^25 outputs
+    ((2391, 16379, 512), True, False), ((2390, 16379, 512), True, True),               # three columns of a piece, 7 * 2^24 in all
+    ((2391, 16377, 512), True, True), ((7172, 16377, 512), True, False),               # one
     ((885, 15512, 512), False, True), ((885, 15360, 512), True, True), ((885, 15512, 256), True, True),    # 61 and 60 column tiles
-    ((1535, 6657, 384), False, True), ((1536, 6657, 384), True, True),                 # 27, 162 tiles of 256x256
-    ((1537, 3328, 512), False, True), ((1536, 3328, 384), True, True), ((1537, 3073, 384), False, True),   # 13 column tiles: 338, 312 and 325 of 128x128
-    ((1536, 4096, 512), False, True), ((1536, 3968, 512), True, True), ((1536, 4096, 384), True, True),    # 16: 384, 372
-    ((4095, 2048, 512), False, True), ((4097, 1800, 512), True, True), ((2048, 4097, 512), True, True),    # 512, 495, 528
+    ((885, 8192, 512), True, True), ((770, 15512, 384), False, True), ((770, 10648, 384), True, True),     # 32; 5.7 and 3.9 MiB
+    ((866, 8320, 512), False, True), ((866, 8321, 512), True, True), ((896, 8192, 512), True, True),       # 33 column tiles: 4.1 MiB
+    ((1400, 4104, 384), False, True), ((1400, 4096, 384), True, True), ((2048, 3080, 512), False, True),   # 17: 1.503; 16; 13: 1.504
+    ((2048, 3064, 512), True, True), ((1152, 6152, 256), False, True), ((2048, 4104, 384), True, True),    # 12; 25: 1.502; 528 of 128x128
 ])
 def test_short_k_leaves_to_the_main_kernel(ds3, shape, store, accumulate, mode):
     f = lambda acc: ds3._L().ds3_gemm_default_kernel(*shape, mode, 0, acc, 0, 256)
