@@ -936,19 +936,21 @@ int tail_share_steps(int tail, int kb, int nslots) {
     return 0;
 }
 
-// Whether cutting a tail tile's `saved` K-steps off a call is worth the exchange of the partial sums (through memory, all
-// of them at the same time).  Asked where the caller names no configuration.  `tail` shared tiles an XCD of `cus` compute
-// units, `per_cu` workgroups on each.
-//   Behind full rounds the exchange costs about 8 K-steps of 256x256 tiles, 6 of 128x128 ones.
-//   Without one, a tail of up to one tile a compute unit leaves half of the workgroup slots idle, and sharing also puts
-//   these to work; the more tiles there are to exchange, the dearer.  Beyond one tile a unit there is less to gain.
+// Whether cutting a tail tile's `kb` K-steps down by `saved` is worth the exchange of the partial sums (through memory, all
+// of them at the same time).  Asked where the caller names no configuration.
+//   Behind full rounds the exchange costs about 8 K-steps of 256x256 tiles, 6 of the 128x128 ones' (`per_cu` = 2 of them on
+//   a compute unit).
+//   Without a full round it costs as much as 16 of them, for sharing also puts a second workgroup on compute units that had
+//   one.  And the runs must not be much longer than half a tile: halves walk K in two groups, each in step, as whole tiles
+//   do, and find their neighbours' operands in the L2; longer runs start anywhere.
 // 15600 calls, operands from HBM and from the caches, every output form, time over that of sharing always (in brackets:
 // the worst, and what is above 1.03): 256x256 behind rounds .968 (1.10, 1%), 128x128 behind rounds .911 (1.05, 1%), no
-// round and up to one a unit .975 (1.15, 1.5%: a long K with all operands from HBM), more .844 (1.17, 1.3%); the better
-// of the two each time .966, .909, .960, .837; 16 to 32 K-steps as the line .986 (1.19, 25%), .912, .978 (1.38, 19%), .843.
-static bool share_pays(int rounds, int tail, int saved, int cus, int per_cu) {
+// round .968 (1.29, 7%) up to one tile a compute unit and .839 (1.17, 3%) beyond; the better of the two each time .966,
+// .909, .960, .837; 16 to 32 K-steps as the line by the number of tiles .986 (1.19, 25%), .912, .978 (1.38, 19%), .843.
+// 98 K-steps without a round, in runs of 84: 2617x1681x12544 by row 118 us shared / 90 not; of 49: 7775x320x12544 60 / 88.
+static bool share_pays(int rounds, int saved, int kb, int per_cu) {
     if (rounds > 0) return saved >= (per_cu > 1 ? 6 : 8);
-    return tail > cus ? saved >= 14 : saved >= 2 && 2 * saved >= tail - 12;
+    return saved >= 16 && 10 * saved >= 3 * kb;
 }
 
 // Bytes of workspace with which a dense launch of configuration C shares its tail tiles
@@ -974,7 +976,7 @@ static size_t share_bytes(int64_t ntiles, int64_t slots, int kb, int* q_main, in
 template <class C>
 static bool share_default(int64_t ntiles, int64_t slots, int kb, int q_main) {
     const int nslots = (int)(slots / 8), cnt = (int)((ntiles + 7) / 8);
-    return q_main > 0 && share_pays(cnt / nslots, cnt % nslots, kb - q_main, nslots / C::WG_PER_CU, C::WG_PER_CU);
+    return q_main > 0 && share_pays(cnt / nslots, kb - q_main, kb, C::WG_PER_CU);
 }
 
 // `named`: the caller chose the configuration; its tail is shared wherever the workspace allows it.

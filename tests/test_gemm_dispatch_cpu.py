@@ -103,8 +103,9 @@ def test_dense_one_tile_a_compute_unit(ds3, shape, few, mode):
 
 
 @pytest.mark.parametrize("shape,c_type,mode,pow2,shared", [
-    ((2048, 2048, 2560), 1, 0, 0, 1), ((2048, 2048, 2432), 1, 0, 0, 0),                # 256 tiles of 128x128: 10 and 9 K-steps saved
-    ((1536, 1408, 12416), 0, 1, 0, 1), ((2048, 1152, 4224), 1, 0, 0, 1),               # 132, 144
+    ((2048, 2048, 4096), 1, 0, 0, 1), ((2048, 2048, 3840), 1, 0, 0, 0),                # 256 tiles of 128x128: 16 of 32 K-steps saved, 15 of 30
+    ((2048, 1152, 6144), 0, 1, 0, 1), ((2048, 1152, 4224), 1, 0, 0, 0),                # 144: 24 of 48, 11 of 33
+    ((1024, 1152, 12800), 1, 0, 0, 1), ((1024, 1152, 15232), 1, 0, 0, 0),              # 72: 50 of 100, 17 of 119 (long runs)
     ((1228, 3404, 1152), 1, 0, 0, 0), ((2048, 2176, 2176), 1, 0, 1, 0),                # more than compute units
     ((2000, 9100, 2048), 0, 1, 0, 1), ((2000, 9100, 1920), 0, 1, 0, 0),                # 288 of 256x256: 8 and 7
     ((3072, 3072, 1536), 0, 1, 1, 1), ((3072, 3072, 1408), 0, 1, 1, 0),                # 576 of 128x128: 6 and 5

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 # the first leaves a partial round of tiles, which the GEMM shares along K through the workspace: the arrival counters
 # are updated by every replay and left ready for the next; the second runs the kernel for few tiles
-@pytest.mark.parametrize("shape,shared", [((2048, 1152, 4224), True), ((384, 640, 1024), False)])
+@pytest.mark.parametrize("shape,shared", [((2048, 1152, 6144), True), ((384, 640, 1024), False)])
 def test_quantize_and_gemm_in_a_captured_graph(ds3, shape, shared):
     announce(f"graph capture {shape}")
     L = ds3._L()

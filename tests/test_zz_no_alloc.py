@@ -21,7 +21,7 @@ def test_no_alloc_entry_point_matches_the_workspace_entry_point(ds3):
     rng = np.random.default_rng(91)
     # the named variant whose tail tiles the first three share along K (144 and 256 tiles of 128 x 128, 288 of 256 x 256);
     # the others share nothing: tiles between the named sizes, and the kernel for few tiles
-    for (m, n, k, shared) in [(2048, 1152, 4224, 2), (2048, 2048, 2560, 2), (2000, 9100, 2048, 0), (1333, 3000, 1536, None),
+    for (m, n, k, shared) in [(2048, 1152, 6144, 2), (2048, 2048, 4096, 2), (2000, 9100, 2048, 0), (1333, 3000, 1536, None),
                               (2048, 1536, 2048, None), (384, 640, 1024, None)]:
         announce(f"no-alloc GEMM {m}x{n}x{k}")
         for ct in (ds3.DS3_F32, ds3.DS3_BF16):
