@@ -311,11 +311,12 @@ int ds3_gemm_tail_share_steps(int tail_tiles, int k_steps, int workgroups);
 int ds3_gemm_few_tiles_config(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
 /* ... whether one that does not accumulate takes the kernel for a short K and a large output (1 or 0), */
 int ds3_gemm_short_k(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, int compute_units);
-/* ... which tile it takes between the variants' sizes (0: 256 weight rows x 192, 1: 192 x 128, 2: 192 x 256; -1: none), */
+/* ... which tile such a call takes between the variants' sizes (0: 256 weight rows x 192, 1: 192 x 128, 2: 192 x 256; -1:
+ * none), */
 int ds3_gemm_between_tile(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int pow2,
                           int compute_units);
-/* ... which kernel that is, for every form of the call: the variant's number, or one of the values below plus the tile's
- * number (as above) or the configuration's (of the kernel for few rows or few tiles); -1: no such call, */
+/* ... which of all these it takes, accumulating or not: a variant's number, or one of the values below plus the number of
+ * the tile between the variants or of the configuration for few rows or few tiles; -1: no such call, */
 enum { DS3_GEMM_KERNEL_BETWEEN = 8, DS3_GEMM_KERNEL_SHORT_K = 16, DS3_GEMM_KERNEL_FEW = 32 };
 int ds3_gemm_default_kernel(int64_t M, int64_t N, int64_t K, ds3_bscale sb_mode, ds3_dtype c_type, int accumulate, int pow2,
                             int compute_units);
